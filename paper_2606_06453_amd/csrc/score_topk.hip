@@ -7,7 +7,10 @@
 //                holds D/16 channels of the summary and of the query view.  Products
 //                accumulate in fp64 and reduce across the row with DPP, then round once to
 //                fp32.  Output goes to a scratch table scores[h][i][j] (rows padded to 4).
-// topk_kernel    One workgroup per (request, KV head).  It runs an exact radix select over
+// topk_bucket_kernel  One workgroup per (request, KV head): the exact selection from scores or from
+//                bounds with re-scoring of the pages they leave undecided, by one histogram of
+//                equal-width bins; topk_wave_kernel does it in one wave for short requests.
+// topk_kernel    (approximate options, and requests past the bucketed kernel's) One workgroup per (request, KV head).  It runs an exact radix select over
 //                an order-preserving uint32 key of the fp32 score.  Passes start at the
 //                highest bit where the candidates' smallest and largest keys differ and take
 //                up to 8 bits each.  Each pass builds a double-buffered LDS histogram, and
@@ -1251,42 +1254,6 @@ __global__ __launch_bounds__(kThreads) void topk_kernel(
   if (h == 0 && tid == 0) sel_count[i] = min(tot_sel, max_sel);
 }
 
-// ------------------------------------------------------------------------------------
-// Two-pass selection for the block-mean score (first pass: kMeanBound).  For each
-// (request, KV head), with K = K_free and B a monotone bucket map of the bounds:
-//   T_lo = K-th largest B(lower), T_hi = (K+1)-th largest B(upper) (over candidates);
-//   B(upper) < T_lo  -> out: K candidates score strictly higher (their fp32 keys too);
-//   B(lower) > T_hi  -> in:  at most K candidates, itself included, can score >= it;
-//   otherwise undecided: re-scored from the fp32 Mean with exact_row_score (the one-pass
-//   arithmetic); the best K - |in| of them by (score desc, page asc) complete the set.
-// Both thresholds come out of one radix walk (two histograms per pass).  Every load of the
-// prologue (both bounds of every page and the group's query rows) is issued before any is
-// used, and the keys stay in registers.
-// ------------------------------------------------------------------------------------
-constexpr int kFusedAppendMaxElems = 8192;  // block rows x channels refreshed in the top-K launch
-constexpr int kTwoPassKeys = 4096;     // = kTwoPassMaxPages
-constexpr int kRounds2 = kTwoPassKeys / (4 * kThreads);  // float4 rounds per thread
-constexpr int kPerThread2 = 4 * kRounds2;                  // 16 pages per thread
-constexpr int kMaxUndecided = 1024;
-
-// Page of this thread's key slot x: four consecutive pages per float4 round, rounds 4*kThreads
-// pages apart.
-__device__ __forceinline__ int slot_page(int x) { return 4 * (int)threadIdx.x + (x & 3) + 4 * kThreads * (x >> 2); }
-
-// Both bound rows of N rounds, every load issued before any is used.  Slots past the
-// request's pages re-read its last float4 (never used), so no row padding is fetched.
-template <int N, bool BOTH>
-__device__ __forceinline__ void load_bounds(const float* lo, const float* up, int P, float4 (&lv)[kRounds2],
-                                            float4 (&uv)[kRounds2]) {
-  const int last4 = ((P + 3) & ~3) - 4;           // P >= 1; the row stride is a multiple of 4 >= P
-#pragma unroll
-  for (int y = 0; y < N; y++) {
-    const int j = min(4 * (int)threadIdx.x + 4 * kThreads * y, last4);
-    lv[y] = *reinterpret_cast<const float4*>(lo + j);
-    if constexpr (BOTH) uv[y] = *reinterpret_cast<const float4*>(up + j);
-  }
-}
-
 struct RadixState {
   uint32_t prefix, pmask;   // resolved high bits of the k-th largest key
   int top;                  // highest unresolved bit, -1 when done
@@ -1304,164 +1271,268 @@ __device__ __forceinline__ RadixState radix_init(uint32_t kmin, uint32_t kmax, i
   r.remaining = k;
   return r;
 }
-__device__ __forceinline__ int radix_shift(const RadixState& r) { return r.top >= 7 ? r.top - 7 : 0; }
+// Digits of up to BITS bits, most significant first.
+template <int BITS>
+__device__ __forceinline__ int radix_shift(const RadixState& r) { return r.top >= BITS - 1 ? r.top - (BITS - 1) : 0; }
+template <int BITS>
 __device__ __forceinline__ uint32_t radix_dmask(const RadixState& r) {
-  return r.top >= 0 ? (1u << (r.top - radix_shift(r) + 1)) - 1u : 0u;
+  return r.top >= 0 ? (1u << (r.top - radix_shift<BITS>(r) + 1)) - 1u : 0u;
 }
 
-// One wave: lane l owns the bins 255-4l .. 252-4l (descending).  Writes the bin that holds the
-// remaining-th largest key and the number of keys in the bins above it.
-__device__ __forceinline__ void wave_pick_bin(const int* hist, int remaining, int* pick) {
-  const int lane = lane_id();
-  int c[4], tot = 0;
-#pragma unroll
-  for (int e = 0; e < 4; e++) {
-    c[e] = hist[255 - 4 * lane - e];
-    tot += c[e];
-  }
-  int above = wave_incl_sum(tot) - tot;
-#pragma unroll
-  for (int e = 0; e < 4; e++) {
-    if (above < remaining && above + c[e] >= remaining) {
-      pick[0] = 255 - 4 * lane - e;
-      pick[1] = above;
-    }
-    above += c[e];
-  }
-}
-
+template <int BITS>
 __device__ __forceinline__ void radix_advance(RadixState& r, const int* pick) {
-  const int sh = radix_shift(r);
+  const int sh = radix_shift<BITS>(r);
   r.remaining -= pick[1];
   r.prefix |= (uint32_t)pick[0] << sh;
-  r.pmask |= radix_dmask(r) << sh;
+  r.pmask |= radix_dmask<BITS>(r) << sh;
   r.top = sh - 1;
 }
 
-// The k-th largest keys of two key sets held in registers (key x of this thread counts when
-// bit x of `cand` is set); both selects share each pass and its barriers.  sb.top < 0 on
-// entry runs the first select alone.
-__device__ __forceinline__ void dual_radix_select(const uint32_t (&ka)[kPerThread2], const uint32_t (&kb)[kPerThread2],
-                                                  uint32_t cand, RadixState& sa, RadixState& sb,
-                                                  int (*hist)[2][256], int (*pick)[2][2]) {
-  const int tid = threadIdx.x, w = tid >> 6;
-  int hb = 0;
-  hist[0][0][tid] = 0;
-  hist[0][1][tid] = 0;
-  __syncthreads();
-  while (sa.top >= 0 || sb.top >= 0) {
-    const int sha = radix_shift(sa), shb = radix_shift(sb);
-    const uint32_t dma = radix_dmask(sa), dmb = radix_dmask(sb);
-    hist[hb ^ 1][0][tid] = 0;
-    hist[hb ^ 1][1][tid] = 0;
+// ------------------------------------------------------------------------------------
+// Selection, one workgroup of T threads per (request, KV head), K pages per thread: thread t
+// holds pages t, t + T, ..., so 64 consecutive pages lie in one wave's lanes of one slot, a ballot
+// is a 64-bit word of page flags, and the words in slot and wave order are the pages in ascending
+// order.  The chosen set is those words in LDS; compacting it takes one wave-wide prefix over
+// their counts, which every wave forms for itself.  What bounds these kernels is latency: a chain
+// of dependent round trips (geometry, bound rows, re-scored summaries) and barriers at few
+// instructions each, so slots past the request's pages are skipped by uniform branches and the
+// shape (T, K) follows the request bound.
+// ------------------------------------------------------------------------------------
+template <int T, int K>
+struct SelShape {
+  static constexpr int W = T / kWave;                  // waves
+  static constexpr int M = T * K;                      // pages
+  static constexpr int kWords = M / kWave;             // flag words
+  static constexpr int G = (kWords + kWave - 1) / kWave;   // words a lane holds in a prefix
+  static_assert(kWave % W == 0, "a slot's words lie in one prefix group");
+};
+
+// Members and exclusive prefix counts of the flag words, as every wave holds them: lane l of
+// group g has word 64 g + l.
+template <int T, int K>
+struct WordPrefix {
+  using S = SelShape<T, K>;
+  uint32_t lo[S::G], hi[S::G];
+  int excl[S::G], total;
+  __device__ __forceinline__ void load(const uint2* words, int nwords) {
+    const int lane = lane_id();
+    total = 0;
 #pragma unroll
-    for (int x = 0; x < kPerThread2; x++) {
-      if ((cand >> x) & 1u) {
-        if (sa.top >= 0 && (ka[x] & sa.pmask) == sa.prefix) atomicAdd(&hist[hb][0][(ka[x] >> sha) & dma], 1);
-        if (sb.top >= 0 && (kb[x] & sb.pmask) == sb.prefix) atomicAdd(&hist[hb][1][(kb[x] >> shb) & dmb], 1);
-      }
+    for (int y = 0; y < S::G; y++) {
+      const int wi = kWave * y + lane;
+      const uint2 v = wi < nwords ? words[wi] : make_uint2(0u, 0u);
+      lo[y] = v.x;
+      hi[y] = v.y;
+      const int c = __popc(v.x) + __popc(v.y);
+      const int incl = wave_incl_sum(c);
+      excl[y] = total + incl - c;
+      total += (int)wave_last((uint32_t)incl);
     }
-    __syncthreads();
-    if (w == 0 && sa.top >= 0) wave_pick_bin(hist[hb][0], sa.remaining, pick[hb][0]);
-    if (w == 1 && sb.top >= 0) wave_pick_bin(hist[hb][1], sb.remaining, pick[hb][1]);
-    __syncthreads();
-    if (sa.top >= 0) radix_advance(sa, pick[hb][0]);
-    if (sb.top >= 0) radix_advance(sb, pick[hb][1]);
-    hb ^= 1;
+  }
+  // This thread's page of slot x (a compile-time constant after unrolling) in wave w: whether it
+  // is a member, and how many members lie below it.
+  __device__ __forceinline__ bool at(int x, int w, int& rank) const {
+    const int y = x * S::W / kWave, src = x * S::W % kWave + w;
+    const uint32_t l = (uint32_t)__builtin_amdgcn_readlane((int)lo[y], src);
+    const uint32_t u = (uint32_t)__builtin_amdgcn_readlane((int)hi[y], src);
+    rank = __builtin_amdgcn_mbcnt_hi(u, __builtin_amdgcn_mbcnt_lo(l, (uint32_t)__builtin_amdgcn_readlane(excl[y], src)));
+    return __builtin_amdgcn_inverse_ballot_w64((uint64_t)u << 32 | l);
+  }
+};
+__device__ __forceinline__ uint2 word_of(uint64_t m) { return make_uint2((uint32_t)m, (uint32_t)(m >> 32)); }
+
+// A wave's own words, one per slot: collected with lane x holding slot x's, stored at once.
+template <int T, int K>
+struct SlotWords {
+  uint32_t lo = 0u, hi = 0u;
+  __device__ __forceinline__ void put(int x, uint64_t m) {
+    const bool mine = lane_id() == x;
+    lo = mine ? (uint32_t)m : lo;
+    hi = mine ? (uint32_t)(m >> 32) : hi;
+  }
+  __device__ __forceinline__ void store(uint2* words, int w, int P) const {
+    const int x = lane_id();
+    if (x < K && x * T < P) words[x * SelShape<T, K>::W + w] = make_uint2(lo, hi);
+  }
+};
+
+// The request's geometry and its share of the selection.
+struct SelArgs {
+  const float* lower;                  // [H][batch][stride] scores, or their lower bounds
+  const float* upper;                  // upper bounds (two-pass kinds)
+  const float* mean;                   // summaries of the re-scoring
+  const uint16_t* maxs;
+  const uint16_t* mins;
+  const uint16_t* q;
+  int Hq, H, qdims, ps, r, max_pages, stride, batch, num_phys;
+  const int32_t* indptr;
+  const int32_t* indices;
+  const int32_t* seq_lens;
+  const int32_t* items;                // page counts of the operator; nullptr: from seq_lens
+  const int32_t* budget;
+  int n_sink, n_local, max_sel;
+  int32_t* sel_pages;
+  int32_t* sel_count;
+};
+struct SelRow {
+  int i, h, base, P, nS, nL, Kfree;
+  bool all;
+  int32_t* out;
+};
+__device__ __forceinline__ SelRow sel_row(const SelArgs& a, int b, int cap) {
+  SelRow s;
+  s.i = b / a.H;
+  s.h = b - s.i * a.H;
+  s.base = a.items ? 0 : a.indptr[s.i];
+  s.P = a.items ? min(min(max(a.items[s.i], 0), a.stride), cap)
+                : num_pages(a.seq_lens[s.i], a.ps, (a.indptr[s.i + 1] - s.base) * a.r, min(a.max_pages, cap));
+  const int Ktot = max(min(a.budget[s.i], a.max_sel), 0);
+  s.all = Ktot >= s.P;
+  s.nS = min(a.n_sink, s.P);
+  s.nL = min(a.n_local, s.P);
+  const int nF = s.all ? s.P : s.nS + s.nL - max(0, s.nS - (s.P - s.nL));
+  s.Kfree = s.all ? 0 : max(0, Ktot - nF);
+  s.out = a.sel_pages + ((int64_t)s.i * a.H + s.h) * a.max_sel;
+  return s;
+}
+
+// Ascending compaction of the chosen words (complete, behind a barrier) into the selection row.
+template <int T, int K>
+__device__ __forceinline__ void write_selection(const SelArgs& a, const SelRow& s, const uint2* words, int w) {
+  using S = SelShape<T, K>;
+  const int tid = (int)threadIdx.x;
+  WordPrefix<T, K> wp;
+  wp.load(words, (s.P + T - 1) / T * S::W);
+#pragma unroll
+  for (int x = 0; x < K; x++) {
+    if (x * T < s.P) {                               // uniform
+      int pos;
+      if (wp.at(x, w, pos) && pos < a.max_sel) s.out[pos] = x * T + tid;
+    }
+  }
+  for (int m = wp.total + tid; m < a.max_sel; m += T) s.out[m] = -1;
+  if (s.h == 0 && tid == 0) a.sel_count[s.i] = min(wp.total, a.max_sel);
+}
+
+constexpr int kBins = 1024;            // histogram bins: 16 per lane of the wave that scans them
+
+// One wave: the bin that holds the k-th largest entry of a histogram of kBins bins, the number of
+// entries above it and its own count, in pick[0..2].  Lane l owns the bins 1023 - 16 l .. 1008 - 16 l.
+__device__ __forceinline__ void wave_pick_bin(const int* hist, int k, int* pick) {
+  constexpr int N = kBins / kWave;
+  const int lane = lane_id();
+  int c[N], tot = 0;
+#pragma unroll
+  for (int e = 0; e < N; e += 4) {
+    const int4 v = *reinterpret_cast<const int4*>(&hist[kBins - N * lane - 4 - e]);
+    c[e] = v.w;
+    c[e + 1] = v.z;
+    c[e + 2] = v.y;
+    c[e + 3] = v.x;
+    tot += (v.x + v.y) + (v.z + v.w);
+  }
+  int above = wave_incl_sum(tot) - tot;
+  if (above < k && above + tot >= k) {               // one lane
+#pragma unroll
+    for (int e = 0; e < N; e++) {
+      if (above < k && above + c[e] >= k) {
+        pick[0] = kBins - 1 - N * lane - e;
+        pick[1] = above;
+        pick[2] = c[e];
+      }
+      above += c[e];
+    }
   }
 }
 
-// The decode step's append inside the selection launch: the workgroup of (request i, KV head h)
-// writes the step's K/V rows of head h at token L - 1 and refreshes that block's summaries with
-// the cache stage's own task code (4 lanes per 8-channel task, as in the decode-step summary
+// The decode step's append inside the selection launch, by workgroups of its own ahead of the
+// selection's: they write the step's K/V rows at token L - 1 and refresh that block's summaries
+// with the cache stage's own task code (4 lanes per 8-channel task, as in the decode-step summary
 // launch), so the cache and the summaries are bit-identical to a separate append.  The block is
-// request i's last one, a forced local block, so the selection never reads its new summary.
+// its request's last one, a forced local block, so the selection never reads its new summary.
 struct AppendStep {
   summ::AppendArgs app;      // app.knew == nullptr: nothing to append
   const void* k;             // the K cache (read)
   float k_scale;
   int kt, ps, D, num_phys;
-  int wgs;                   // one-wave selection launch: 0, the selection workgroup appends its
-                             // head; > 0, this many workgroups per request past the selection's
-                             // append all of the request's heads
   int max_pages;             // blocks per request bound
   float* mean;
   uint16_t* mean_bf;
   uint16_t* maxo;
   uint16_t* mino;
 };
-template <int KT, int NT>
-__device__ __forceinline__ void append_head_kt(const AppendStep& ap, int i, int h, int H, int bs, int r, int base,
-                                               int L, const int32_t* __restrict__ indices) {
-  const int chunks = ap.D / 8, j = (L - 1) / bs, slice = (int)threadIdx.x & 3;
-  for (int t0 = 0; t0 < chunks; t0 += NT / 4) {             // uniform: full quads
-    const int c8 = t0 + (int)threadIdx.x / 4;
-    const bool active = c8 < chunks;
-    summ::task<4, KT, true>(ap.k, ap.k_scale, ap.num_phys, H, ap.ps, bs, r, ap.D, indices, base, L, i, j, h,
-                            active ? c8 : 0, active, slice, ap.mean, ap.mean_bf, ap.maxo, ap.mino, ap.app);
-  }
-}
-// NT: the workgroup's thread count.  P: the request's block count; a request whose token L - 1
-// lies in no listed block (L = 0, a short page list) appends nothing, as in the cache stage's
-// own append launch.
-template <int NT = kThreads>
-__device__ __forceinline__ void append_head(const AppendStep& ap, int i, int h, int H, int bs, int r, int base, int L,
-                                            int P, const int32_t* __restrict__ indices) {
-  if (L < 1 || (L - 1) / bs >= P) return;
-  if (ap.kt == kKvFp8E4M3) append_head_kt<kKvFp8E4M3, NT>(ap, i, h, H, bs, r, base, L, indices);
-  else if (ap.kt == kKvFp8E5M2) append_head_kt<kKvFp8E5M2, NT>(ap, i, h, H, bs, r, base, L, indices);
-  else append_head_kt<kKvBf16, NT>(ap, i, h, H, bs, r, base, L, indices);
-}
+// Append workgroups per request in a launch of T-thread workgroups: T / 4 tasks each.
+template <int T>
+__host__ __device__ constexpr int append_wgs(int H, int D) { return (H * (D / 8) + T / 4 - 1) / (T / 4); }
 
-// The one-wave selection launch's append workgroups (blocks of more than kFusedAppendMaxElems
-// elements): ap.wgs workgroups per request share the tasks (KV head, 8-channel chunk) of the
-// request's block L - 1, kWave / 4 tasks each, with the cache stage's task code and load batch,
-// so the summaries are bit-identical to its append launch.
-template <int KT, int KB>
-__device__ __forceinline__ void append_spread_kt(const AppendStep& ap, int a, int H, int bs, int r,
-                                                 const int32_t* __restrict__ indptr,
-                                                 const int32_t* __restrict__ indices,
-                                                 const int32_t* __restrict__ seq_lens) {
-  const int i = a / ap.wgs;
+// Append workgroup a: its share of the tasks (KV head, 8-channel chunk) of its request's block
+// L - 1.  A request whose token L - 1 lies in no listed block (L = 0, a short page list) appends
+// nothing, as in the cache stage's own append launch.
+template <int T, int KT, int KB>
+__device__ __forceinline__ void append_tasks_kt(const AppendStep& ap, int a, int H, int bs, int r,
+                                                const int32_t* __restrict__ indptr,
+                                                const int32_t* __restrict__ indices,
+                                                const int32_t* __restrict__ seq_lens) {
+  const int wgs = append_wgs<T>(H, ap.D), i = a / wgs;
   const int L = seq_lens[i], base = indptr[i];
   const int P = num_pages(L, bs, (indptr[i + 1] - base) * r, ap.max_pages);
   if (L < 1 || (L - 1) / bs >= P) return;
   const int chunks = ap.D / 8;
-  const int t = (a - i * ap.wgs) * (kWave / 4) + (int)threadIdx.x / 4;   // the same for a quad's lanes
+  const int t = (a - i * wgs) * (T / 4) + (int)threadIdx.x / 4;          // the same for a quad's lanes
   const bool active = t < H * chunks;
   const int tk = active ? t : 0, h = tk / chunks;
   summ::task<4, KT, true, KB>(ap.k, ap.k_scale, ap.num_phys, H, ap.ps, bs, r, ap.D, indices, base, L, i,
                               (L - 1) / bs, h, tk - h * chunks, active, (int)threadIdx.x & 3, ap.mean, ap.mean_bf,
                               ap.maxo, ap.mino, ap.app);
 }
-__device__ __forceinline__ void append_spread(const AppendStep& ap, int a, int H, int bs, int r,
-                                              const int32_t* __restrict__ indptr, const int32_t* __restrict__ indices,
-                                              const int32_t* __restrict__ seq_lens) {
-  // blocks of 64 tokens: a lane's 16 rows in one round trip, as in the append launch
-  if (bs > 4 * summ::kBatch) {
-    if (ap.kt == kKvFp8E4M3) append_spread_kt<kKvFp8E4M3, 2 * summ::kBatch>(ap, a, H, bs, r, indptr, indices, seq_lens);
-    else if (ap.kt == kKvFp8E5M2) append_spread_kt<kKvFp8E5M2, 2 * summ::kBatch>(ap, a, H, bs, r, indptr, indices, seq_lens);
-    else append_spread_kt<kKvBf16, 2 * summ::kBatch>(ap, a, H, bs, r, indptr, indices, seq_lens);
-  } else {
-    if (ap.kt == kKvFp8E4M3) append_spread_kt<kKvFp8E4M3, summ::kBatch>(ap, a, H, bs, r, indptr, indices, seq_lens);
-    else if (ap.kt == kKvFp8E5M2) append_spread_kt<kKvFp8E5M2, summ::kBatch>(ap, a, H, bs, r, indptr, indices, seq_lens);
-    else append_spread_kt<kKvBf16, summ::kBatch>(ap, a, H, bs, r, indptr, indices, seq_lens);
-  }
+// KB: token rows a lane loads per round trip (the order of the sums does not depend on it).
+template <int T, int KB>
+__device__ __forceinline__ void append_tasks(const AppendStep& ap, int a, int H, int bs, int r,
+                                             const int32_t* __restrict__ indptr, const int32_t* __restrict__ indices,
+                                             const int32_t* __restrict__ seq_lens) {
+  if (ap.kt == kKvFp8E4M3) append_tasks_kt<T, kKvFp8E4M3, KB>(ap, a, H, bs, r, indptr, indices, seq_lens);
+  else if (ap.kt == kKvFp8E5M2) append_tasks_kt<T, kKvFp8E5M2, KB>(ap, a, H, bs, r, indptr, indices, seq_lens);
+  else append_tasks_kt<T, kKvBf16, KB>(ap, a, H, bs, r, indptr, indices, seq_lens);
 }
 
+// ------------------------------------------------------------------------------------
+// Exact selection.  For each (request, KV head), with K = K_free and B a monotone map of the
+// bounds onto kBins bins of equal width between the smallest candidate lower bound and the
+// largest candidate upper bound:
+//   T_lo = K-th largest B(lower), T_hi = (K+1)-th largest B(upper) (over candidates);
+//   B(upper) < T_lo  -> out: K candidates score strictly higher (their fp32 keys too);
+//   B(lower) > T_hi  -> in:  at most K candidates, itself included, can score >= it;
+//   otherwise undecided: ranked by its exact score; the best K - |in| of them by (score desc,
+//   page asc) complete the set.
+// B is non-decreasing, so the classification is as rigorous on bins as on the floats.  One pass
+// of kBins bins leaves at most a few pages per bin at the threshold for up to 16 pages per bin of
+// spread-out scores; finer bins would not narrow the bounds.
 // RK = kMeanDot: the two-pass block-mean selection (bounds in, fp32 Mean rows of D channels for
-// the re-scoring).  RK = an envelope kind: the two-pass selection of that kind (bounds in, bf16
-// Max and Min rows of D channels for the re-scoring, g <= 4).  RK = kNoRescore: exact scores
-// (lower == upper == the scores); the pages of the threshold buckets are ranked by their own
-// scores and nothing is re-scored.
-template <int RK, int D>
-__global__ __launch_bounds__(kThreads) void topk_bucket_kernel(
-    const float* __restrict__ lower, const float* __restrict__ upper, const float* __restrict__ mean,
-    const uint16_t* __restrict__ maxs, const uint16_t* __restrict__ mins, const uint16_t* __restrict__ q, int Hq,
-    int H, int qdims, int ps, int r, int max_pages, int stride, int batch, int num_phys,
-    const int32_t* __restrict__ indptr, const int32_t* __restrict__ indices, const int32_t* __restrict__ seq_lens,
-    const int32_t* __restrict__ budget, int n_sink, int n_local, int max_sel, int32_t* __restrict__ sel_pages,
-    int32_t* __restrict__ sel_count, const AppendStep ap) {
+// the re-scoring with exact_row_score, the one-pass arithmetic).  RK = an envelope kind: the
+// two-pass selection of that kind (bounds in, bf16 Max and Min rows of D channels for the
+// re-scoring, g <= 4).  RK = kNoRescore: exact scores (lower == upper == the scores); the
+// undecided pages are ranked by their own scores.
+// Up to a wave of undecided pages is ranked by one wave; more (near-ties, or skewed scores such as
+// the NSA softmax, which put most candidates in the lowest bins) by a radix select over the exact
+// keys.  More than kMaxUndecided pages to re-score: every candidate is re-scored instead.
+// What bounds it is instruction issue (the active-instruction counter covers 8 of the 12 us on 512
+// pairs) behind a chain of five round trips: few operations per page slot matter more than their
+// latency.  Kernel trace, against 16-bit bucket keys found in two 256-bin passes by four waves of 16
+// slots per thread, each appending its own head first: 512 pairs of up to 2048 pages, two-pass block
+// mean 17.3 -> 12.6 us; 128 pairs of 4096 pages, two-pass Quest 15.9 -> 11.3; 1024 pairs of up to
+// 4096 pages, Max 16.9 -> 12.1; 512 pairs of NSA scores 28.7 -> 12.5; 32 pairs of 2048 pages 10.1 ->
+// 5.0.
+// ------------------------------------------------------------------------------------
+constexpr int kMaxUndecided = 1024;
+
+// Six waves per SIMD (80 VGPRs) where the re-scoring allows it: the registers the compiler would
+// otherwise take for the append workgroups' divisions cost the selection its residency, and a grid
+// that is not resident at once leaves the dispatcher in the middle of a round over the CUs, which
+// upsets the decode launch's pairing of long and short requests per CU (1024 pairs: decode 36.5 us
+// after a selection at four waves per SIMD, 34.2 us at six).
+template <int RK, int D, int T, int K>
+__global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(D > 128 ? 2 : K > 8 && RK != kNoRescore ? 4 : 6))) void topk_bucket_kernel(const SelArgs a, const AppendStep ap) {
+  using S = SelShape<T, K>;
   constexpr bool kMeanRescore = RK == kMeanDot;
   constexpr bool kEnvRescore = is_env(RK);
   constexpr bool kRescore = kMeanRescore || kEnvRescore;
@@ -1471,89 +1542,71 @@ __global__ __launch_bounds__(kThreads) void topk_bucket_kernel(
   constexpr int E = DD / 16;
   // 16-byte query chunks of a group: g <= 16 heads (block mean), g <= 4 (envelope kinds)
   constexpr int kQChunks = kMeanRescore ? 16 * D / 8 : kEnvRescore ? 4 * D / 8 : 1;
-  constexpr int kQRounds = (kQChunks + kThreads - 1) / kThreads;
-  __shared__ uint32_t exact_keys[kTwoPassKeys];   // only after a bound overflow
-  __shared__ __align__(16) uint8_t status[kTwoPassKeys];   // 0 out, 1 chosen, 2 undecided
-  __shared__ int und[kMaxUndecided];              // undecided pages
-  __shared__ uint32_t und_key[kMaxUndecided];     // their exact keys
+  constexpr int kQRounds = (kQChunks + T - 1) / T;
+  __shared__ __align__(16) int hist[2][kBins];
+  __shared__ uint2 words[S::kWords];              // chosen pages
+  __shared__ uint2 eq_words[S::kWords];           // radix select: the pages of the threshold key
+  __shared__ uint32_t exact_keys[kRescore ? S::M : 1];   // re-scored keys by page (more than a wave of them)
+  __shared__ int und[kRescore ? kMaxUndecided : kWave];  // undecided pages
+  __shared__ uint32_t und_key[kWave];             // their exact keys (up to a wave of them)
   __shared__ uint4 qraw[kMeanRescore ? kQChunks : 1];   // the group's bf16 query rows
   __shared__ double qbar[kMeanRescore ? D : 1];   // group-mean query, channel order
   __shared__ float qs[kEnvRescore ? 4 * D : 1];   // the group's query rows, fp32 in row order
-  __shared__ int hist[2][2][256];
-  __shared__ int pick[2][2][2];
-  __shared__ uint32_t mm[4][kThreads / kWave];
-  __shared__ int wave_tot[kThreads / kWave];
+  __shared__ int pick[2][3];
+  __shared__ uint32_t mm[2][S::W];
   __shared__ int counters[2];                     // |in|, |undecided|
 
-  const int tid = threadIdx.x, lane = lane_id(), w = tid >> 6;
-  const int i = blockIdx.x / H, h = blockIdx.x % H;
-  const int base = indptr[i];
-  const int P = num_pages(seq_lens[i], ps, (indptr[i + 1] - base) * r, min(max_pages, kTwoPassKeys));
-  if (ap.app.knew) append_head(ap, i, h, H, ps, r, base, seq_lens[i], P, indices);
-  int Ktot = budget[i];
-  Ktot = Ktot < max_sel ? Ktot : max_sel;
-  Ktot = Ktot < 0 ? 0 : Ktot;
-  int32_t* out = sel_pages + ((int64_t)i * H + h) * max_sel;
-  const bool all = Ktot >= P;
-  const int nS = min(n_sink, P), nL = min(n_local, P);
-  const int nF = all ? P : nS + nL - max(0, nS - (P - nL));
-  const int Kfree = all ? 0 : max(0, Ktot - nF);
-  const int g = Hq / H;
+  const int n_app = ap.app.knew ? a.batch * append_wgs<T>(a.H, ap.D) : 0;
+  if ((int)blockIdx.x < n_app) {                  // uniform: an append workgroup
+    append_tasks<T, 4>(ap, (int)blockIdx.x, a.H, a.ps, a.r, a.indptr, a.indices, a.seq_lens);
+    return;
+  }
+  const int tid = (int)threadIdx.x, lane = lane_id();
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const SelRow s = sel_row(a, (int)blockIdx.x - n_app, S::M);
+  const int P = s.P, g = a.Hq / a.H;
+  auto is_cand = [&](int j) { return !s.all && j >= s.nS && j < P - s.nL; };
 
-  for (int j = tid; j < P; j += kThreads) status[j] = (all || is_forced(j, P, nS, nL)) ? 1 : 0;
-  if (tid < 2) counters[tid] = 0;
-  int need = 0, n_und = 0;
-  bool rescore_all = false;
-  uint32_t cand = 0;                               // bit x: slot_page(x) is a candidate
-  if (Kfree > 0) {
+  if (s.Kfree > 0) {
     // every prologue load in one round trip: both bound rows and the group's query rows
-    const float* lo = lower + ((int64_t)h * batch + i) * stride;
-    const float* up = upper + ((int64_t)h * batch + i) * stride;
-    float4 lv[kRounds2], uv[kRounds2];
-    const int rounds = (P + 4 * kThreads - 1) / (4 * kThreads);
-    if (rounds <= 1) load_bounds<1, kRescore>(lo, up, P, lv, uv);
-    else if (rounds <= 2) load_bounds<2, kRescore>(lo, up, P, lv, uv);
-    else load_bounds<kRounds2, kRescore>(lo, up, P, lv, uv);
-    if constexpr (!kRescore) {
+    const int64_t row = ((int64_t)s.h * a.batch + s.i) * a.stride;
+    float lf[K], uf[kRescore ? K : 1];
 #pragma unroll
-      for (int y = 0; y < kRounds2; y++) uv[y] = lv[y];
+    for (int x = 0; x < K; x++) {
+      if (x * T < P) {                               // uniform; lanes past P re-read the last page
+        const int j = min(x * T + tid, P - 1);
+        lf[x] = a.lower[row + j];
+        if constexpr (kRescore) uf[x] = a.upper[row + j];
+      }
     }
     const int nq = g * DD / 8;
     uint4 qv[kQRounds];
     if constexpr (kRescore) {
-      const uint4* qsrc = reinterpret_cast<const uint4*>(q + ((int64_t)i * Hq + (int64_t)h * g) * D);
+      const uint4* qsrc = reinterpret_cast<const uint4*>(a.q + ((int64_t)s.i * a.Hq + (int64_t)s.h * g) * D);
 #pragma unroll
-      for (int t = 0; t < kQRounds; t++) qv[t] = qsrc[min(tid + kThreads * t, nq - 1)];
+      for (int t = 0; t < kQRounds; t++) qv[t] = qsrc[min(tid + T * t, nq - 1)];
     }
-
-    // Bucket keys: B(x) = floor((x - lo) * 65535 / (hi - lo)), clamped to [0, 65535], with lo
-    // the smallest candidate lower bound and hi the largest upper bound.  B is monotone
-    // (non-decreasing) in x, so the classification below is as rigorous on buckets as on
-    // the floats themselves, and 16-bit keys spread over their range need only two passes.
-    float lf[kPerThread2], uf[kPerThread2];
+    for (int x = tid; x < 2 * kBins / 4; x += T) reinterpret_cast<int4*>(&hist[0][0])[x] = make_int4(0, 0, 0, 0);
+    if (tid < 2) counters[tid] = 0;
     float lo_min = INFINITY, hi_max = -INFINITY;
 #pragma unroll
-    for (int x = 0; x < kPerThread2; x++) {
-      const int j = slot_page(x);
-      const float4 l4 = lv[x >> 2], u4 = uv[x >> 2];
-      lf[x] = (x & 3) == 0 ? l4.x : (x & 3) == 1 ? l4.y : (x & 3) == 2 ? l4.z : l4.w;
-      uf[x] = (x & 3) == 0 ? u4.x : (x & 3) == 1 ? u4.y : (x & 3) == 2 ? u4.z : u4.w;
-      if ((x >> 2) < rounds && j < P && !is_forced(j, P, nS, nL)) {
-        cand |= 1u << x;
+    for (int x = 0; x < K; x++) {
+      if (x * T < P && is_cand(x * T + tid)) {
         lo_min = fminf(lo_min, lf[x]);
-        hi_max = fmaxf(hi_max, uf[x]);
+        if constexpr (kRescore) hi_max = fmaxf(hi_max, uf[x]);
+        else hi_max = fmaxf(hi_max, lf[x]);
       }
     }
     if constexpr (kMeanRescore) {
 #pragma unroll
       for (int t = 0; t < kQRounds; t++)
-        if (tid + kThreads * t < nq) qraw[tid + kThreads * t] = qv[t];
+        if (tid + T * t < nq) qraw[tid + T * t] = qv[t];
     } else if constexpr (kEnvRescore) {
       // the envelope scores' query layout: head r, channel c at (r 16 + u) E + e, c the RowMap
       // channel (u, cc, e)
 #pragma unroll
       for (int t = 0; t < kQRounds; t++) {
-        const int x = tid + kThreads * t;
+        const int x = tid + T * t;
         if (x < nq) {
           const uint32_t ws[4] = {qv[t].x, qv[t].y, qv[t].z, qv[t].w};
 #pragma unroll
@@ -1574,154 +1627,172 @@ __global__ __launch_bounds__(kThreads) void topk_bucket_kernel(
     }
     __syncthreads();
 #pragma unroll
-    for (int x = 0; x < kThreads / kWave; x++) {
+    for (int x = 0; x < S::W; x++) {
       lo_min = fminf(lo_min, __uint_as_float(mm[0][x]));
       hi_max = fmaxf(hi_max, __uint_as_float(mm[1][x]));
     }
     const float span = hi_max - lo_min;
-    const float scale = (span > 0.f && span < INFINITY) ? 65535.f / span : 0.f;
-    uint32_t kl[kPerThread2], ku[kPerThread2];
+    const float scale = (span > 0.f && span < INFINITY) ? (float)kBins / span : 0.f;
+    // NaN bounds (and any with scale 0) fall into bin 0
+    auto bin_of = [&](float x) { return (int)fminf(fmaxf((x - lo_min) * scale, 0.f), (float)(kBins - 1)); };
+    int bl[K], bu[kRescore ? K : 1];
 #pragma unroll
-    for (int x = 0; x < kPerThread2; x++) {
-      kl[x] = (uint32_t)(int)fminf(fmaxf((lf[x] - lo_min) * scale, 0.f), 65535.f);
-      ku[x] = (uint32_t)(int)fminf(fmaxf((uf[x] - lo_min) * scale, 0.f), 65535.f);
+    for (int x = 0; x < K; x++) {
+      if (x * T < P) {
+        bl[x] = bin_of(lf[x]);
+        if constexpr (kRescore) bu[x] = bin_of(uf[x]);
+        if (is_cand(x * T + tid)) {
+          atomicAdd(&hist[0][bl[x]], 1);
+          if constexpr (kRescore) atomicAdd(&hist[1][bu[x]], 1);
+        }
+      }
     }
     if constexpr (kMeanRescore) {
       // group-mean query: fp64 sums in head order, then finish_qbar's division (as one pass)
       const uint16_t* qh = reinterpret_cast<const uint16_t*>(qraw);
-      for (int c = tid; c < D; c += kThreads) {
+      for (int c = tid; c < D; c += T) {
         double acc = 0.0;
         for (int r = 0; r < g; r++) acc += (double)bf16lo(qh[r * D + c]);
-        qbar[c] = c < qdims ? finish_qbar_one(acc, g) : 0.0;
+        qbar[c] = c < a.qdims ? finish_qbar_one(acc, g) : 0.0;
       }
-    }
-    RadixState sl = radix_init(0u, 0xffffu, Kfree), su = radix_init(0u, 0xffffu, Kfree + 1);
-    dual_radix_select(kl, ku, cand, sl, su, hist, pick);
-    const uint32_t t_lo = sl.prefix;                 // bucket of the K-th largest lower bound
-    const uint32_t t_hi = su.prefix;                 // bucket of the (K+1)-th largest upper bound
-    // each round's four consecutive pages in one 32-bit status store (forced pages stay chosen);
-    // the chosen count and the undecided list grow by one atomic per wave
-    int my_in = 0;
-    uint32_t und_bits = 0;                           // bit x: slot_page(x) is undecided
-    uint32_t word[kRounds2] = {};
-#pragma unroll
-    for (int x = 0; x < kPerThread2; x++) {
-      const int j = slot_page(x);
-      uint32_t st = (j < P && is_forced(j, P, nS, nL)) ? 1u : 0u;
-      if ((cand >> x) & 1u) {
-        if (kl[x] > t_hi) {
-          st = 1u;
-          my_in++;
-        } else if (ku[x] >= t_lo) {
-          st = 2u;
-          und_bits |= 1u << x;
-        }
-      }
-      word[x >> 2] |= st << (8 * (x & 3));
-    }
-#pragma unroll
-    for (int y = 0; y < kRounds2; y++)
-      if (y < rounds) *reinterpret_cast<uint32_t*>(&status[4 * tid + 4 * kThreads * y]) = word[y];
-    my_in = (int)wave_last((uint32_t)wave_incl_sum(my_in));
-    if (lane == 0 && my_in) atomicAdd(&counters[0], my_in);
-    const int n_mine = __popc(und_bits);
-    const int und_incl = wave_incl_sum(n_mine);
-    const int und_wave = (int)wave_last((uint32_t)und_incl);
-    int und_base = 0;
-    if (lane == kWave - 1 && und_wave) und_base = atomicAdd(&counters[1], und_wave);
-    int pos = __builtin_amdgcn_readlane(und_base, kWave - 1) + und_incl - n_mine;
-    while (und_bits) {
-      const int x = __builtin_ctz(und_bits);
-      und_bits &= und_bits - 1u;
-      const int j = slot_page(x);
-      float lx = 0.f;
-#pragma unroll
-      for (int z = 0; z < kPerThread2; z++) lx = z == x ? lf[z] : lx;   // lf[x] without a dynamic index
-      if constexpr (!kRescore) exact_keys[j] = float_key(lx);           // the exact score
-      if (pos < kMaxUndecided) {
-        und[pos] = j;
-        if constexpr (!kRescore) und_key[pos] = float_key(lx);
-      }
-      pos++;
     }
     __syncthreads();
-    need = Kfree - counters[0];
-    n_und = counters[1];
-    rescore_all = n_und > kMaxUndecided;
-    if (rescore_all) {
-      // pathological overlap of the bounds: re-score every candidate instead
+    // at least K_free + 1 candidates exist: P > K_total
+    if (w == 0) wave_pick_bin(hist[0], s.Kfree, pick[0]);
+    if (w == S::W - 1) wave_pick_bin(hist[kRescore ? 1 : 0], s.Kfree + 1, pick[1]);
+    __syncthreads();
+    const int t_lo = pick[0][0];                     // bin of the K-th largest lower bound
+    const int t_hi = pick[1][0];                     // bin of the (K+1)-th largest upper bound
+    uint32_t um = 0;                                 // bit x: the page of slot x is undecided
+    uint64_t mu[K];                                  // this wave's undecided pages of slot x
+    int n_in = 0, n_mine = 0;                        // this wave's counts
+    SlotWords<T, K> sw;
 #pragma unroll
-      for (int x = 0; x < kPerThread2; x++) {
-        if ((cand >> x) & 1u) {
-          status[slot_page(x)] = 2;
-          if constexpr (!kRescore) exact_keys[slot_page(x)] = float_key(lf[x]);
+    for (int x = 0; x < K; x++) {
+      mu[x] = 0;
+      if (x * T < P) {
+        const int j = x * T + tid;
+        const bool cand = is_cand(j);
+        bool u = bl[x] >= t_lo;
+        if constexpr (kRescore) u = bu[x] >= t_lo;
+        const bool in = cand && bl[x] > t_hi;
+        u = u && cand && !in;
+        um |= u ? 1u << x : 0u;
+        mu[x] = __ballot(u);
+        n_in += __popcll(__ballot(in));
+        n_mine += __popcll(mu[x]);
+        sw.put(x, __ballot(in || (j < P && !cand)));   // forced pages are chosen
+      }
+    }
+    sw.store(words, w, P);
+    int at = 0;
+    if (lane == 0) {
+      if (n_in) atomicAdd(&counters[0], n_in);
+      if (n_mine) at = atomicAdd(&counters[1], n_mine);
+    }
+    if (n_mine) {                                    // uniform over the wave
+      at = __builtin_amdgcn_readfirstlane(at);
+#pragma unroll
+      for (int x = 0; x < K; x++) {
+        if (mu[x]) {
+          const int pos = at + __builtin_amdgcn_mbcnt_hi((uint32_t)(mu[x] >> 32),
+                                                         __builtin_amdgcn_mbcnt_lo((uint32_t)mu[x], 0u));
+          if ((um >> x) & 1u) {
+            if constexpr (kRescore) {
+              if (pos < kMaxUndecided) und[pos] = x * T + tid;
+            } else if (pos < kWave) {
+              und[pos] = x * T + tid;
+              und_key[pos] = float_key(lf[x]);
+            }
+          }
+          at += __popcll(mu[x]);
         }
       }
-      need = Kfree;
-      __syncthreads();
     }
-  }
-
-  // exact scores of the undecided pages: rows of 16 lanes, two pages per row at a time
-  const int n_score = rescore_all ? P : n_und;
-  if (need > 0) {
-    if constexpr (kRescore) {
-    const int row = tid >> 4, u = tid & 15;
-    double qb[kMeanRescore ? E : 1];
-    if constexpr (kMeanRescore) {
+    __syncthreads();
+    int need = s.Kfree - counters[0];
+    const int n_und = counters[1];
+    if (need > 0 && need >= n_und) {                 // every undecided page is chosen
 #pragma unroll
-      for (int c = 0; c < M::kChunks; c++)
-#pragma unroll
-        for (int e = 0; e < 4; e++) qb[4 * c + e] = qbar[M::channel(u, c, e)];
-    }
-    for (int x0 = row; x0 < n_score; x0 += 2 * kRows) {
-      const int x1 = x0 + kRows;
-      const bool has1 = x1 < n_score;
-      const int j0 = rescore_all ? x0 : und[x0];
-      const int j1 = has1 ? (rescore_all ? x1 : und[x1]) : j0;
-      const int64_t p0 = block_row(indices + base, j0, r, num_phys);
-      const int64_t p1 = block_row(indices + base, j1, r, num_phys);
-      float s0, s1;
-      if constexpr (kMeanRescore) {
-        uint32_t w0[RowWords<DD, false>::W], w1[RowWords<DD, false>::W];
-        load_row_words<DD, false>(mean + (p0 * H + h) * D, u, w0);
-        load_row_words<DD, false>(mean + (p1 * H + h) * D, u, w1);
-        s0 = exact_row_score<DD, false>(qb, w0);
-        s1 = exact_row_score<DD, false>(qb, w1);
-      } else {
-        constexpr int W = RowWords<DD, true>::W;
-        uint32_t a0[W], a1[W], b0[needs_min(RK) ? W : 1], b1[needs_min(RK) ? W : 1];
-        load_row_words<DD, true>(maxs + (p0 * H + h) * D, u, a0);
-        load_row_words<DD, true>(maxs + (p1 * H + h) * D, u, a1);
-        if constexpr (needs_min(RK)) {
-          load_row_words<DD, true>(mins + (p0 * H + h) * D, u, b0);
-          load_row_words<DD, true>(mins + (p1 * H + h) * D, u, b1);
-          s0 = (float)env_exact<RK, DD>(qs, 0, g, u, a0, b0);
-          s1 = (float)env_exact<RK, DD>(qs, 0, g, u, a1, b1);
-        } else {
-          s0 = (float)env_exact<RK, DD>(qs, 0, g, u, a0, a0);
-          s1 = (float)env_exact<RK, DD>(qs, 0, g, u, a1, a1);
+      for (int x = 0; x < K; x++) {
+        if (mu[x] && lane == 0) {
+          uint2& v = words[x * S::W + w];
+          v = make_uint2(v.x | (uint32_t)mu[x], v.y | (uint32_t)(mu[x] >> 32));
         }
       }
-      if (u == 0) {
-        if (rescore_all) {
-          exact_keys[j0] = float_key(s0);               // forced pages' keys are never read
-          if (has1) exact_keys[j1] = float_key(s1);
-        } else {
-          und_key[x0] = float_key(s0);
-          exact_keys[j0] = float_key(s0);
-          if (has1) {
-            und_key[x1] = float_key(s1);
-            exact_keys[j1] = float_key(s1);
+    } else if (need > 0) {
+      const bool rescore_all = kRescore && n_und > kMaxUndecided;
+      if (rescore_all) {
+        // pathological overlap of the bounds: re-score every candidate instead
+        need = s.Kfree;
+        um = 0;
+        SlotWords<T, K> fw;
+#pragma unroll
+        for (int x = 0; x < K; x++) {
+          if (x * T < P) {
+            const int j = x * T + tid;
+            const bool cand = is_cand(j);
+            um |= cand ? 1u << x : 0u;
+            fw.put(x, __ballot(j < P && !cand));
           }
         }
+        fw.store(words, w, P);
       }
-    }
-    __syncthreads();
-    }
-    if (!rescore_all && n_und <= kWave) {
-      // rank among the undecided by (key desc, page asc); the best `need` are chosen
-      {
+      // exact scores of the undecided pages: rows of 16 lanes, two pages per row at a time
+      if constexpr (kRescore) {
+        constexpr int kRowsT = T / 16;
+        const int n_score = rescore_all ? P : n_und;
+        const int row16 = tid >> 4, u = tid & 15;
+        double qb[kMeanRescore ? E : 1];
+        if constexpr (kMeanRescore) {
+#pragma unroll
+          for (int c = 0; c < M::kChunks; c++)
+#pragma unroll
+            for (int e = 0; e < 4; e++) qb[4 * c + e] = qbar[M::channel(u, c, e)];
+        }
+        for (int x0 = row16; x0 < n_score; x0 += 2 * kRowsT) {
+          const int x1 = x0 + kRowsT;
+          const bool has1 = x1 < n_score;
+          const int j0 = rescore_all ? x0 : und[x0];
+          const int j1 = has1 ? (rescore_all ? x1 : und[x1]) : j0;
+          const int64_t p0 = block_row(a.indices + s.base, j0, a.r, a.num_phys);
+          const int64_t p1 = block_row(a.indices + s.base, j1, a.r, a.num_phys);
+          float s0, s1;
+          if constexpr (kMeanRescore) {
+            uint32_t w0[RowWords<DD, false>::W], w1[RowWords<DD, false>::W];
+            load_row_words<DD, false>(a.mean + (p0 * a.H + s.h) * D, u, w0);
+            load_row_words<DD, false>(a.mean + (p1 * a.H + s.h) * D, u, w1);
+            s0 = exact_row_score<DD, false>(qb, w0);
+            s1 = exact_row_score<DD, false>(qb, w1);
+          } else {
+            constexpr int WW = RowWords<DD, true>::W;
+            uint32_t a0[WW], a1[WW], b0[needs_min(RK) ? WW : 1], b1[needs_min(RK) ? WW : 1];
+            load_row_words<DD, true>(a.maxs + (p0 * a.H + s.h) * D, u, a0);
+            load_row_words<DD, true>(a.maxs + (p1 * a.H + s.h) * D, u, a1);
+            if constexpr (needs_min(RK)) {
+              load_row_words<DD, true>(a.mins + (p0 * a.H + s.h) * D, u, b0);
+              load_row_words<DD, true>(a.mins + (p1 * a.H + s.h) * D, u, b1);
+              s0 = (float)env_exact<RK, DD>(qs, 0, g, u, a0, b0);
+              s1 = (float)env_exact<RK, DD>(qs, 0, g, u, a1, b1);
+            } else {
+              s0 = (float)env_exact<RK, DD>(qs, 0, g, u, a0, a0);
+              s1 = (float)env_exact<RK, DD>(qs, 0, g, u, a1, a1);
+            }
+          }
+          if (u == 0) {
+            if (n_und <= kWave) {
+              und_key[x0] = float_key(s0);
+              if (has1) und_key[x1] = float_key(s1);
+            } else {
+              exact_keys[j0] = float_key(s0);       // forced pages' keys are never read
+              if (has1) exact_keys[j1] = float_key(s1);
+            }
+          }
+        }
+        __syncthreads();
+      }
+      if (n_und <= kWave) {
+        // rank among the undecided by (key desc, page asc); the best `need` are chosen
         if (w == 0) {
           // composite (key, ~page): larger is better; the others' composites come as LDS
           // broadcasts, four per step, so the loads of a step are in flight together
@@ -1736,89 +1807,99 @@ __global__ __launch_bounds__(kThreads) void topk_bucket_kernel(
             rank += (c0 > cx) + (c1 > cx) + (c2 > cx) + (c3 > cx);
           }
           for (; y < n_und; y++) rank += comp(y) > cx;
-          if (mine) status[jx] = rank < need ? 1 : 0;
+          if (mine && rank < need)
+            atomicOr(reinterpret_cast<unsigned int*>(words) + (jx >> 5), 1u << (jx & 31));
         }
-      }
-    } else {
-      // exact radix select over the exact keys of the undecided pages (status 2): every
-      // candidate after a bound overflow (need = K_free), else the pages of the threshold
-      // buckets when more than a wave of them is left (skewed scores, such as the NSA softmax,
-      // put most candidates there); ranking them pairwise would cost n^2
-      const int kk = rescore_all ? Kfree : need;
-      uint32_t ke[kPerThread2];
-      uint32_t sm = 0;                               // bit x: slot_page(x) is undecided
-      uint32_t kmin = 0xffffffffu, kmax = 0u;
+      } else {
+        // radix select over the exact keys of the undecided pages, 10-bit digits from the highest
+        // bit in which the extreme keys differ
+        uint32_t ke[K];
+        uint32_t kmin = 0xffffffffu, kmax = 0u;
 #pragma unroll
-      for (int x = 0; x < kPerThread2; x++) {
-        const int j = slot_page(x);
-        const bool in = ((cand >> x) & 1u) && status[j] == 2;
-        ke[x] = in ? exact_keys[j] : 0u;
-        if (in) {
-          sm |= 1u << x;
-          kmin = min(kmin, ke[x]);
-          kmax = max(kmax, ke[x]);
+        for (int x = 0; x < K; x++) {
+          ke[x] = 0u;
+          if ((um >> x) & 1u) {
+            if constexpr (kRescore) ke[x] = exact_keys[x * T + tid];
+            else ke[x] = float_key(lf[x]);
+            kmin = min(kmin, ke[x]);
+            kmax = max(kmax, ke[x]);
+          }
         }
-      }
-      kmin = wave_min_u32(kmin);
-      kmax = wave_max_u32(kmax);
-      if (lane == 0) {
-        mm[0][w] = kmin;
-        mm[1][w] = kmax;
-      }
-      __syncthreads();
+        kmin = wave_min_u32(kmin);
+        kmax = wave_max_u32(kmax);
+        if (lane == 0) {
+          mm[0][w] = kmin;
+          mm[1][w] = kmax;
+        }
+        for (int x = tid; x < kBins / 4; x += T) reinterpret_cast<int4*>(&hist[0][0])[x] = make_int4(0, 0, 0, 0);
+        __syncthreads();
 #pragma unroll
-      for (int x = 0; x < kThreads / kWave; x++) {
-        kmin = min(kmin, mm[0][x]);
-        kmax = max(kmax, mm[1][x]);
-      }
-      RadixState se = radix_init(kmin, kmax, kk), none;
-      none.top = -1;
-      dual_radix_select(ke, ke, sm, se, none, hist, pick);
-      const uint32_t kth = se.prefix;
-      // strictly better pages are in; equal keys go in by page order
-      const int R = (P + kThreads - 1) / kThreads;
-      const int j_lo = min(P, tid * R), j_hi = min(P, j_lo + R);
-      int n_gt = 0, n_eq = 0;
-      for (int j = j_lo; j < j_hi; j++) {
-        if (status[j] != 2) continue;
-        n_gt += exact_keys[j] > kth;
-        n_eq += exact_keys[j] == kth;
-      }
-      int tot_gt, tot_eq;
-      block_incl_scan(n_gt, wave_tot, &tot_gt);
-      int eq_rank = block_incl_scan(n_eq, wave_tot, &tot_eq) - n_eq;
-      for (int j = j_lo; j < j_hi; j++) {
-        if (status[j] != 2) continue;
-        const bool ch = exact_keys[j] > kth || (exact_keys[j] == kth && eq_rank++ < kk - tot_gt);
-        status[j] = ch ? 1 : 0;
+        for (int x = 0; x < S::W; x++) {
+          kmin = min(kmin, mm[0][x]);
+          kmax = max(kmax, mm[1][x]);
+        }
+        RadixState rs = radix_init(kmin, kmax, need);
+        int hb = 0;
+        while (rs.top >= 0) {                        // uniform
+          const int sh = radix_shift<10>(rs);
+          const uint32_t dm = radix_dmask<10>(rs);
+          for (int x = tid; x < kBins / 4; x += T)
+            reinterpret_cast<int4*>(&hist[hb ^ 1][0])[x] = make_int4(0, 0, 0, 0);
+#pragma unroll
+          for (int x = 0; x < K; x++)
+            if (((um >> x) & 1u) && (ke[x] & rs.pmask) == rs.prefix) atomicAdd(&hist[hb][(ke[x] >> sh) & dm], 1);
+          __syncthreads();
+          if (w == 0) wave_pick_bin(hist[hb], rs.remaining, pick[hb]);
+          __syncthreads();
+          radix_advance<10>(rs, pick[hb]);
+          if (pick[hb][2] == rs.remaining) break;    // every key with this prefix is chosen
+          hb ^= 1;
+        }
+        // above the threshold prefix: chosen; equal to it: the `remaining` lowest pages
+#pragma unroll
+        for (int x = 0; x < K; x++) {
+          if (x * T < P) {
+            const bool u = (um >> x) & 1u;
+            const uint32_t mk = ke[x] & rs.pmask;
+            const uint64_t gt = __ballot(u && mk > rs.prefix), eq = __ballot(u && mk == rs.prefix);
+            if (lane == 0) {
+              uint2& v = words[x * S::W + w];
+              v = make_uint2(v.x | (uint32_t)gt, v.y | (uint32_t)(gt >> 32));
+              eq_words[x * S::W + w] = word_of(eq);
+            }
+          }
+        }
+        __syncthreads();
+        WordPrefix<T, K> ep;
+        ep.load(eq_words, (P + T - 1) / T * S::W);
+#pragma unroll
+        for (int x = 0; x < K; x++) {
+          if (x * T < P) {
+            int rank;
+            const bool e = ep.at(x, w, rank);
+            const uint64_t m = __ballot(e && rank < rs.remaining);
+            if (m && lane == 0) {
+              uint2& v = words[x * S::W + w];
+              v = make_uint2(v.x | (uint32_t)m, v.y | (uint32_t)(m >> 32));
+            }
+          }
+        }
       }
     }
-  } else if (n_und > 0) {
-    for (int x = tid; x < n_und; x += kThreads) status[und[x]] = 0;   // need == 0
+  } else {
+    // every page, or the forced pages alone
+    SlotWords<T, K> sw;
+#pragma unroll
+    for (int x = 0; x < K; x++) {
+      if (x * T < P) {
+        const int j = x * T + tid;
+        sw.put(x, __ballot(j < P && !is_cand(j)));
+      }
+    }
+    sw.store(words, w, P);
   }
   __syncthreads();
-
-  // ascending compaction of the chosen pages: thread t reads the status bytes of pages
-  // [16 t, 16 t + 16) in one 16-byte load (kThreads * 16 = kTwoPassKeys)
-  static_assert(kThreads * 16 == kTwoPassKeys, "one 16-byte status load per thread");
-  uint32_t chosen = 0;                             // bit e: page 16 tid + e
-  {
-    const uint4 w = *reinterpret_cast<const uint4*>(&status[16 * tid]);
-    const uint32_t ws[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-    for (int e = 0; e < 16; e++)
-      chosen |= (((ws[e >> 2] >> (8 * (e & 3))) & 0xffu) == 1u && 16 * tid + e < P) ? (1u << e) : 0u;
-  }
-  int tot_sel;
-  int pos = block_incl_scan(__popc(chosen), wave_tot, &tot_sel) - __popc(chosen);
-  while (chosen) {
-    const int e = __builtin_ctz(chosen);
-    chosen &= chosen - 1u;
-    if (pos < max_sel) out[pos] = 16 * tid + e;
-    pos++;
-  }
-  for (int m = tot_sel + tid; m < max_sel; m += kThreads) out[m] = -1;
-  if (h == 0 && tid == 0) sel_count[i] = min(tot_sel, max_sel);
+  write_selection<T, K>(a, s, words, w);
 }
 
 // The same exact one-pass selection for requests of at most kWaveMaxPages blocks, by one wave per
@@ -1826,10 +1907,8 @@ __global__ __launch_bounds__(kThreads) void topk_bucket_kernel(
 // 8l .. 8l + 7, an MSB-first radix select over 8-bit digits (a 256-bin LDS histogram per pass,
 // starting below the bits that every candidate key shares) finds the K_free-th largest
 // candidate key, and a prefix over the lanes, which hold the blocks in ascending order, places
-// the equal keys by block index and compacts the chosen blocks.  With the decode step's append
-// in the launch, either each selection workgroup appends its KV head (append_head), or, for
-// blocks too large for that (AppendStep::wgs > 0), the workgroups past the batch's pairs append
-// (append_spread) while the selection workgroups run.
+// the equal keys by block index and compacts the chosen blocks.  The decode step's append runs in
+// workgroups of its own ahead of the selection's.
 constexpr int kWaveMaxPages = 512;
 constexpr int kWaveKeys = kWaveMaxPages / kWave;   // keys per lane
 
@@ -1845,12 +1924,16 @@ __global__ __launch_bounds__(kWave) void topk_wave_kernel(
     const int32_t* __restrict__ budget, int n_sink, int n_local, int max_sel, int32_t* __restrict__ sel_pages,
     int32_t* __restrict__ sel_count, const AppendStep ap) {
   __shared__ __align__(16) int hist[256];
-  if ((int)blockIdx.x >= batch * H) {      // uniform: an append workgroup
-    append_spread(ap, (int)blockIdx.x - batch * H, H, ps, r, indptr, indices, seq_lens);
+  const int n_app = ap.app.knew ? batch * append_wgs<kWave>(H, ap.D) : 0;
+  if ((int)blockIdx.x < n_app) {           // uniform: an append workgroup
+    // blocks of 64 tokens: a lane's 16 rows in one round trip, as in the append launch
+    if (ps > 4 * summ::kBatch) append_tasks<kWave, 2 * summ::kBatch>(ap, (int)blockIdx.x, H, ps, r, indptr, indices, seq_lens);
+    else append_tasks<kWave, summ::kBatch>(ap, (int)blockIdx.x, H, ps, r, indptr, indices, seq_lens);
     return;
   }
   const int lane = lane_id();
-  const int i = blockIdx.x / H, h = blockIdx.x % H;
+  const int pair = (int)blockIdx.x - n_app;
+  const int i = pair / H, h = pair - i * H;
   // the score row loads with the request's geometry: lane l reads blocks 8l .. 8l + 7, clamped
   // into the row (stride >= 4 floats; entries past the request's blocks are never used)
   const float* row = scores + ((int64_t)h * batch + i) * stride;
@@ -1858,7 +1941,6 @@ __global__ __launch_bounds__(kWave) void topk_wave_kernel(
   const float4 sb = *reinterpret_cast<const float4*>(row + min(kWaveKeys * lane + 4, stride - 4));
   const int base = indptr[i];
   const int P = num_pages(seq_lens[i], ps, (indptr[i + 1] - base) * r, min(max_pages, kWaveMaxPages));
-  if (ap.app.knew && ap.wgs == 0) append_head<kWave>(ap, i, h, H, ps, r, base, seq_lens[i], P, indices);
   int Ktot = budget[i];
   Ktot = Ktot < max_sel ? Ktot : max_sel;
   Ktot = Ktot < 0 ? 0 : Ktot;
@@ -1886,8 +1968,8 @@ __global__ __launch_bounds__(kWave) void topk_wave_kernel(
     }
     RadixState s = radix_init(wave_min_u32(kmin), wave_max_u32(kmax), Kfree);
     while (s.top >= 0) {                   // uniform over the wave
-      const int sh = radix_shift(s);
-      const uint32_t dm = radix_dmask(s);
+      const int sh = radix_shift<8>(s);
+      const uint32_t dm = radix_dmask<8>(s);
       *reinterpret_cast<int4*>(&hist[4 * lane]) = make_int4(0, 0, 0, 0);
       __syncthreads();
 #pragma unroll
@@ -1913,7 +1995,7 @@ __global__ __launch_bounds__(kWave) void topk_wave_kernel(
       }
       const int src = __builtin_ctzll(__ballot(bin >= 0));
       const int pk[2] = {__builtin_amdgcn_readlane(bin, src), __builtin_amdgcn_readlane(bin_above, src)};
-      radix_advance(s, pk);
+      radix_advance<8>(s, pk);
       __syncthreads();                     // the histogram read before the next pass clears it
     }
     kth = s.prefix;
@@ -2106,6 +2188,28 @@ void launch_score(const ScoreArgs& a, hipStream_t stream) {
   else hipLaunchKernelGGL((score_kernel<KIND, D, false>), dim3((unsigned)grid), dim3(kThreads), lds, stream, a);
 }
 
+// The bucketed selection's shape: as many threads as keep a request's pages at four slots each
+// while the batch's (request, KV head) pairs leave CUs idle; fewer and longer waves when the pairs
+// fill the chip by themselves, because every wave repeats the prefixes and reductions.  Kernel
+// trace, us at T = 1024 / 512 / 256: 32 pairs of 2048 pages 5.3 / 5.8 / 6.6, 128 pairs of 4096 pages
+// 11.1 / 11.7 / 15.0, 512 pairs of 2048 pages 21.8 / 13.8 / 14.0, 1024 pairs of 4096 pages 22.9 /
+// 13.3 / 12.9.  Unused slots cost too: 512 pairs of up to 2048 pages of NSA scores at T = 512 take
+// 13.0 us with four slots, 14.2 with eight.
+template <int RK, int D, int T, int K>
+void launch_bucket_shape(const SelArgs& a, const AppendStep& ap, hipStream_t stream) {
+  const int grid = a.batch * a.H + (ap.app.knew ? a.batch * append_wgs<T>(a.H, ap.D) : 0);
+  hipLaunchKernelGGL((topk_bucket_kernel<RK, D, T, K>), dim3(grid), dim3(T), 0, stream, a, ap);
+}
+template <int RK, int D>
+void launch_bucket(const SelArgs& a, const AppendStep& ap, hipStream_t stream) {
+  const long long pairs = (long long)a.batch * a.H, cus = device_cus();
+  if (a.max_pages <= 1024) launch_bucket_shape<RK, D, 256, 4>(a, ap, stream);
+  else if (a.max_pages <= 2048 && pairs <= 2 * cus) launch_bucket_shape<RK, D, 512, 4>(a, ap, stream);
+  else if (D <= 128 && 2 * pairs <= cus) launch_bucket_shape<RK, D <= 128 ? D : 64, 1024, 4>(a, ap, stream);
+  else if (pairs <= 2 * cus) launch_bucket_shape<RK, D, 512, 8>(a, ap, stream);
+  else launch_bucket_shape<RK, D, 256, 16>(a, ap, stream);
+}
+
 }  // namespace
 
 int device_cus() {
@@ -2158,21 +2262,18 @@ hipError_t launch_score_topk(const Geometry& g, const uint16_t* q, int Hq, int k
   const int ik = internal_kind(kind);
   // the selection paths: the block mean's two passes, the envelope kinds' two passes, else one
   // pass of scores (through a flow for NSA and smoothing) selected by the one-wave kernel up to
-  // kWaveMaxPages blocks per request, the bucketed kernel up to kTwoPassKeys, else the radix kernel
+  // kWaveMaxPages blocks per request, the bucketed kernel up to kTwoPassMaxPages, else the radix kernel
   const bool mean_two_pass = (kind == kMeanDot || kind == kAbiContent) && mean_bf && !approx;
   const bool env_two_pass =
-      is_env(ik) && !approx && g.max_pages <= kTwoPassKeys && Hq <= 4 * g.H && (g.Dqk == 64 || g.Dqk == 128);
+      is_env(ik) && !approx && g.max_pages <= kTwoPassMaxPages && Hq <= 4 * g.H && (g.Dqk == 64 || g.Dqk == 128);
   const bool flow = kind == kAbiNsa || kind == kAbiSmooth;
   const bool wave = !approx && !mean_two_pass && !env_two_pass && g.max_pages <= kWaveMaxPages;
-  // The step's append: inside the top-K launch, or first of all when the selection reads every
-  // block's score (the flows couple the pages; the radix path is not fused).  A block too large
-  // for one workgroup to refresh in the selection's shadow (a 64-token block of 576 channels)
-  // gets workgroups of its own in the one-wave selection launch, or else a launch of its own
-  // ahead of the selection.
-  const bool spread = wave && !flow && g.bs * g.Dqk > kFusedAppendMaxElems;
+  // The step's append: workgroups of its own inside the selection launch, or a launch ahead of
+  // everything when the selection reads every block's score (the flows couple the pages; the
+  // radix path is not fused).
   AppendStep ap{};
   if (sa.k_new) {
-    if (approx || g.max_pages > kTwoPassKeys || flow || (g.bs * g.Dqk > kFusedAppendMaxElems && !spread)) {
+    if (approx || g.max_pages > kTwoPassMaxPages || flow) {
       const hipError_t e =
           launch_kv_append_summarize(g, sa.k_new, sa.v_new, sa.mean, sa.mean_bf, sa.maxo, sa.mino, stream);
       if (e != hipSuccess) return e;
@@ -2189,7 +2290,6 @@ hipError_t launch_score_topk(const Geometry& g, const uint16_t* q, int Hq, int k
       ap.maxo = sa.maxo;
       ap.mino = sa.mino;
       ap.max_pages = g.max_pages;
-      ap.wgs = spread ? (g.H * (g.Dqk / 8) + kWave / 4 - 1) / (kWave / 4) : 0;
     }
   }
   ScoreArgs a;
@@ -2211,52 +2311,60 @@ hipError_t launch_score_topk(const Geometry& g, const uint16_t* q, int Hq, int k
   a.stride = score_stride(g.max_pages);
   a.plane = (int64_t)g.H * g.batch * a.stride;
   a.qdims = kind == kAbiContent ? g.Dv : g.Dqk;
-  if (mean_two_pass) {
-    a.maxs = mean_bf;
-    if (g.Dqk == 64) launch_score<kMeanBound, 64>(a, stream);
-    else if (g.Dqk == 128) launch_score<kMeanBound, 128>(a, stream);
-    else launch_score<kMeanBound, 576>(a, stream);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    const float* upper = scores + a.plane;
-#define VX_TWO_PASS(DD)                                                                                           \
-  hipLaunchKernelGGL((topk_bucket_kernel<kMeanDot, DD>), dim3(g.batch * g.H), dim3(kThreads), 0, stream, scores,  \
-                     upper, mean, nullptr, nullptr, q, Hq, g.H, a.qdims, g.bs, g.r, g.max_pages, a.stride, g.batch, \
-                     g.num_phys_pages, g.indptr, g.indices, g.seq_lens, budget, n_sink, n_local, max_sel, sel_pages, \
-                     sel_count, ap)
-    if (g.Dqk == 64) VX_TWO_PASS(64);
-    else if (g.Dqk == 128) VX_TWO_PASS(128);
-    else VX_TWO_PASS(576);
-#undef VX_TWO_PASS
-    return hipGetLastError();
-  }
-  if (env_two_pass) {
-    // the envelope kinds' exact two-pass selection: fp32 bound pass, then re-scoring of the
-    // undecided pages in the bucketed select
-    switch (ik) {
-#define VX_ENV_TWO_PASS(K)                                                                                          \
-  case K:                                                                                                          \
-    if (g.Dqk == 64) {                                                                                             \
-      launch_score<bound_of_env(K), 64>(a, stream);                                                                \
-      hipLaunchKernelGGL((topk_bucket_kernel<K, 64>), dim3(g.batch * g.H), dim3(kThreads), 0, stream, scores,      \
-                         scores + a.plane, nullptr, maxs, mins, q, Hq, g.H, a.qdims, g.bs, g.r, g.max_pages, a.stride, \
-                         g.batch, g.num_phys_pages, g.indptr, g.indices, g.seq_lens, budget, n_sink, n_local,      \
-                         max_sel, sel_pages, sel_count, ap);                                                       \
-    } else {                                                                                                       \
-      launch_score<bound_of_env(K), 128>(a, stream);                                                               \
-      hipLaunchKernelGGL((topk_bucket_kernel<K, 128>), dim3(g.batch * g.H), dim3(kThreads), 0, stream, scores,     \
-                         scores + a.plane, nullptr, maxs, mins, q, Hq, g.H, a.qdims, g.bs, g.r, g.max_pages, a.stride, \
-                         g.batch, g.num_phys_pages, g.indptr, g.indices, g.seq_lens, budget, n_sink, n_local,      \
-                         max_sel, sel_pages, sel_count, ap);                                                       \
-    }                                                                                                              \
+  SelArgs t{};
+  t.lower = t.upper = scores;
+  t.mean = mean;
+  t.maxs = maxs;
+  t.mins = mins;
+  t.q = q;
+  t.Hq = Hq;
+  t.H = g.H;
+  t.qdims = a.qdims;
+  t.ps = g.bs;
+  t.r = g.r;
+  t.max_pages = g.max_pages;
+  t.stride = a.stride;
+  t.batch = g.batch;
+  t.num_phys = g.num_phys_pages;
+  t.indptr = g.indptr;
+  t.indices = g.indices;
+  t.seq_lens = g.seq_lens;
+  t.budget = budget;
+  t.n_sink = n_sink;
+  t.n_local = n_local;
+  t.max_sel = max_sel;
+  t.sel_pages = sel_pages;
+  t.sel_count = sel_count;
+  if (mean_two_pass || env_two_pass) {
+    // a bound pass, then re-scoring of the undecided pages in the bucketed select
+    t.upper = scores + a.plane;
+    if (mean_two_pass) a.maxs = mean_bf;
+#define VX_TWO_PASS(BK, RK, DD)          \
+  do {                                   \
+    launch_score<BK, DD>(a, stream);     \
+    const hipError_t e = hipGetLastError(); \
+    if (e != hipSuccess) return e;       \
+    launch_bucket<RK, DD>(t, ap, stream); \
+  } while (0)
+#define VX_ENV_TWO_PASS(K)                                             \
+  case K:                                                              \
+    if (g.Dqk == 64) VX_TWO_PASS(bound_of_env(K), K, 64);              \
+    else VX_TWO_PASS(bound_of_env(K), K, 128);                         \
     break;
+    switch (ik) {
+      case kMeanDot:
+        if (g.Dqk == 64) VX_TWO_PASS(kMeanBound, kMeanDot, 64);
+        else if (g.Dqk == 128) VX_TWO_PASS(kMeanBound, kMeanDot, 128);
+        else VX_TWO_PASS(kMeanBound, kMeanDot, 576);
+        break;
       VX_ENV_TWO_PASS(kQuest)
       VX_ENV_TWO_PASS(kQuestConsensus)
       VX_ENV_TWO_PASS(kEnvLower)
       VX_ENV_TWO_PASS(kQuestRectified)
-#undef VX_ENV_TWO_PASS
       default: break;
     }
+#undef VX_ENV_TWO_PASS
+#undef VX_TWO_PASS
     return hipGetLastError();
   }
   if (kind == kAbiNsa || kind == kAbiSmooth) {
@@ -2276,17 +2384,14 @@ hipError_t launch_score_topk(const Geometry& g, const uint16_t* q, int Hq, int k
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (wave) {
-    const int grid = g.batch * g.H + (ap.app.knew ? g.batch * ap.wgs : 0);
+    const int grid = g.batch * g.H + (ap.app.knew ? g.batch * append_wgs<kWave>(g.H, g.Dqk) : 0);
     hipLaunchKernelGGL(topk_wave_kernel, dim3(grid), dim3(kWave), 0, stream, scores, g.H, g.bs, g.r,
                        g.max_pages, a.stride, g.batch, g.indptr, g.indices, g.seq_lens, budget, n_sink, n_local,
                        max_sel, sel_pages, sel_count, ap);
     return hipGetLastError();
   }
-  if (g.max_pages <= kTwoPassKeys && !approx) {
-    hipLaunchKernelGGL((topk_bucket_kernel<kNoRescore, 0>), dim3(g.batch * g.H), dim3(kThreads), 0, stream, scores,
-                       scores, nullptr, nullptr, nullptr, nullptr, Hq, g.H, g.Dqk, g.bs, g.r, g.max_pages, a.stride,
-                       g.batch, g.num_phys_pages, g.indptr, g.indices, g.seq_lens, budget, n_sink, n_local, max_sel,
-                       sel_pages, sel_count, ap);
+  if (g.max_pages <= kTwoPassMaxPages && !approx) {
+    launch_bucket<kNoRescore, 0>(t, ap, stream);
     return hipGetLastError();
   }
   hipLaunchKernelGGL(topk_kernel, dim3(g.batch * g.H), dim3(kThreads), 0, stream, scores, g.H, g.bs, g.r,
