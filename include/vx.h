@@ -256,7 +256,7 @@ typedef struct {
  * pages_budget [batch] int32 is the total page budget of each request, forced pages
  * included.  Requires 0 <= n_sink, 0 <= n_local, n_sink + n_local <= max_sel, and
  * num_q_heads * head_dim_qk <= 16384 (the query block is staged in LDS).
- * MEAN_DOT or MEAN_DOT_CONTENT with `mean_bf16` (and max_pages_per_seq <= 4096) selects in two
+ * MEAN_DOT or MEAN_DOT_CONTENT with `mean_bf16` (and max_pages_per_seq <= 16384) selects in two
  * exact passes; the bf16 copy is otherwise ignored.
  *   1. An approximate score s' = qbar . bf16(Mean) is computed from half the bytes, with a
  *      rigorous bound |s - s'| <= b, where b comes from the bf16 rounding of each channel plus
@@ -267,7 +267,7 @@ typedef struct {
  *      as the one-pass path.
  * The result is identical to the one-pass selection.
  * The four envelope kinds (QUEST, QUEST_CONSENSUS, ENVELOPE_LOWER, QUEST_RECTIFIED) with at
- * most 4 query heads per KV head, head_dim_qk 64 or 128 and max_pages_per_seq <= 4096 (and
+ * most 4 query heads per KV head, head_dim_qk 64 or 128 and max_pages_per_seq <= 16384 (and
  * no approximate options) always select in two exact passes the same way: the first pass sums
  * the exact products in fp32 and bounds the error by 2^-18 |q_r|_1 max_c(|Max_c|, |Min_c|) per
  * head, and the undecided pages are re-scored with the one-pass fp64 arithmetic.
@@ -298,7 +298,7 @@ vx_status vx_page_score_topk(const void* q, int32_t num_q_heads,
  * score launch reads that block's summary from before the append, and only that block's
  * (unused) score depends on it.  The append's workgroups are their own, ahead of the selection's
  * in the launch.  With n_local == 0, NSA or MEAN_DOT_SMOOTH (whose flows couple the blocks), an
- * approximate selection (opt) or more than 4096 blocks per request, the call appends first and
+ * approximate selection (opt) or more than 16384 blocks per request, the call appends first and
  * then selects, in three launches.
  * Arguments and requirements are those of the two calls (mean, mean_bf16, max and min are
  * written by the append and read by the selection; seq_lens counts the new token, so every

@@ -1531,7 +1531,7 @@ constexpr int kMaxUndecided = 1024;
 // upsets the decode launch's pairing of long and short requests per CU (1024 pairs: decode 36.5 us
 // after a selection at four waves per SIMD, 34.2 us at six).
 template <int RK, int D, int T, int K>
-__global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(D > 128 ? 2 : K > 8 && RK != kNoRescore ? 4 : 6))) void topk_bucket_kernel(const SelArgs a, const AppendStep ap) {
+__global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(D > 128 ? 2 : K > 8 && (T > 256 || RK != kNoRescore) ? 4 : 6))) void topk_bucket_kernel(const SelArgs a, const AppendStep ap) {
   using S = SelShape<T, K>;
   constexpr bool kMeanRescore = RK == kMeanDot;
   constexpr bool kEnvRescore = is_env(RK);
@@ -2194,7 +2194,10 @@ void launch_score(const ScoreArgs& a, hipStream_t stream) {
 // trace, us at T = 1024 / 512 / 256: 32 pairs of 2048 pages 5.3 / 5.8 / 6.6, 128 pairs of 4096 pages
 // 11.1 / 11.7 / 15.0, 512 pairs of 2048 pages 21.8 / 13.8 / 14.0, 1024 pairs of 4096 pages 22.9 /
 // 13.3 / 12.9.  Unused slots cost too: 512 pairs of up to 2048 pages of NSA scores at T = 512 take
-// 13.0 us with four slots, 14.2 with eight.
+// 13.0 us with four slots, 14.2 with eight.  Past 4096 pages (up to kTwoPassMaxPages) the selection
+// stays here because the two-pass kinds then read half the summary bytes and the general radix
+// kernel re-reads the scores: block mean of eight requests of 6000 to 8192 pages, score + selection
+// 42.2 + 25.6 us in one pass with the radix kernel, 22 + 11 here (the whole call 66.8 -> 37.5 us).
 template <int RK, int D, int T, int K>
 void launch_bucket_shape(const SelArgs& a, const AppendStep& ap, hipStream_t stream) {
   const int grid = a.batch * a.H + (ap.app.knew ? a.batch * append_wgs<T>(a.H, ap.D) : 0);
@@ -2205,9 +2208,17 @@ void launch_bucket(const SelArgs& a, const AppendStep& ap, hipStream_t stream) {
   const long long pairs = (long long)a.batch * a.H, cus = device_cus();
   if (a.max_pages <= 1024) launch_bucket_shape<RK, D, 256, 4>(a, ap, stream);
   else if (a.max_pages <= 2048 && pairs <= 2 * cus) launch_bucket_shape<RK, D, 512, 4>(a, ap, stream);
-  else if (D <= 128 && 2 * pairs <= cus) launch_bucket_shape<RK, D <= 128 ? D : 64, 1024, 4>(a, ap, stream);
-  else if (pairs <= 2 * cus) launch_bucket_shape<RK, D, 512, 8>(a, ap, stream);
-  else launch_bucket_shape<RK, D, 256, 16>(a, ap, stream);
+  else if (D <= 128 && a.max_pages <= 4096 && 2 * pairs <= cus)
+    launch_bucket_shape<RK, D <= 128 ? D : 64, 1024, 4>(a, ap, stream);
+  else if (a.max_pages <= 4096 && pairs <= 2 * cus) launch_bucket_shape<RK, D, 512, 8>(a, ap, stream);
+  else if (a.max_pages <= 4096) launch_bucket_shape<RK, D, 256, 16>(a, ap, stream);
+  else if constexpr (D > 128) {          // 1024 threads leave too few registers for the re-scoring
+    if (a.max_pages <= 8192) launch_bucket_shape<RK, D, 512, 16>(a, ap, stream);
+    else launch_bucket_shape<RK, D, 512, 32>(a, ap, stream);
+  } else {
+    if (a.max_pages <= 8192) launch_bucket_shape<RK, D, 1024, 8>(a, ap, stream);
+    else launch_bucket_shape<RK, D, 1024, 16>(a, ap, stream);
+  }
 }
 
 }  // namespace

@@ -61,7 +61,7 @@ hipError_t launch_kv_append_summarize(const Geometry& g, const void* k_new, cons
 // mean_bf != nullptr (MEAN_DOT only, max_pages <= kTwoPassMaxPages) selects the exact
 // two-pass path: a bounded first pass over the bf16 means, then fp32 re-scoring of the
 // undecided pages.
-constexpr int kTwoPassMaxPages = 4096;
+constexpr int kTwoPassMaxPages = 16384;
 // remap / tau_q / seed other than 0: the approximate radix top-k of vx_topk_select on the
 // one-pass scores (the two-pass block-mean path and the bucketed selection are exact only).
 // The decode step's cache stage carried by the selection launch: k_new / v_new rows appended

@@ -33,7 +33,7 @@ def kv_dtype_code(t: torch.Tensor) -> int:
     if t.dtype not in codes:
         raise TypeError(f"KV cache dtype {t.dtype} is not bfloat16, float8_e4m3fn or float8_e5m2")
     return codes[t.dtype]
-TWO_PASS_MAX_PAGES = 4096     # block-mean two-pass selection: max_pages_per_seq bound
+TWO_PASS_MAX_PAGES = 16384    # block-mean two-pass selection: blocks per request bound
 # Below this many summary rows (batch x blocks per request x KV heads) the decoder scores the
 # block mean in one pass: the bound pass saves half the summary bytes, but its re-scoring of the
 # undecided pages adds a dependent round trip to the top-K kernel, which a short score stream does

@@ -1,5 +1,5 @@
 """The bucketed selection at the edges of its workgroup shapes (pages per request around a power of
-two, few and many (request, KV head) pairs) on scores where its rules matter: exact ties, skewed
+two, up to its last and the first past it, few and many (request, KV head) pairs) on scores where its rules matter: exact ties, skewed
 scores, infinities.  The scores are planted: the query reads channel 0 alone, so a block's score is
 its summary's channel 0, exactly, and the oracle selects from the same numbers."""
 import numpy as np
@@ -53,7 +53,8 @@ def _select(scores, lens, budget, kind, two_pass, n_sink, n_local, max_sel):
 
 @pytest.mark.parametrize("dist", ["normal", "equal", "skewed", "coarse"])
 @pytest.mark.parametrize("P,B,H", [(513, 3, 2), (1024, 3, 2), (1025, 3, 2), (2048, 2, 4), (2049, 2, 2), (4096, 2, 1),
-                                   (1030, 40, 16), (1500, 33, 16), (2500, 33, 16)])
+                                   (1030, 40, 16), (1500, 33, 16), (2500, 33, 16), (4097, 2, 2), (8192, 2, 1),
+                                   (8193, 2, 1), (16384, 2, 1), (16385, 2, 1)])
 @pytest.mark.parametrize("kind,two_pass", [(vx.MAX_DOT, False), (vx.MEAN_DOT, True), (vx.QUEST, True)])
 def test_selection_shapes(kind, two_pass, P, B, H, dist):
     if dist == "coarse" and kind != vx.MAX_DOT:
