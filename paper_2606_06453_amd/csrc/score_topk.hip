@@ -10,11 +10,12 @@
 // topk_bucket_kernel  One workgroup per (request, KV head): the exact selection from scores or from
 //                bounds with re-scoring of the pages they leave undecided, by one histogram of
 //                equal-width bins; topk_wave_kernel does it in one wave for short requests.
-// topk_kernel    (approximate options, and requests past the bucketed kernel's) One workgroup per (request, KV head).  It runs an exact radix select over
+// topk_radix_kernel  The options' radix selection on the same page slots.
+// topk_long_kernel  (requests past the slots of both) One workgroup per (request, KV head).  It runs an exact radix select over
 //                an order-preserving uint32 key of the fp32 score.  Passes start at the
 //                highest bit where the candidates' smallest and largest keys differ and take
 //                up to 8 bits each.  Each pass builds a double-buffered LDS histogram, and
-//                one wave scans its bins.  Keys stay cached in LDS, and all score loads are
+//                one wave scans its bins.  Each pass re-reads the scores; all score loads are
 //                issued in one round trip.  That finds the K_free-th best candidate.
 //                Ties at the threshold go to the lowest page index.  Each thread owns a
 //                contiguous page range: one block scan ranks the tied pages and a second
@@ -897,8 +898,6 @@ __device__ __forceinline__ bool is_forced(int j, int P, int n_sink, int n_local)
   return j < n_sink || j >= P - n_local;
 }
 
-constexpr int kMaxLdsKeys = 8192;      // candidates kept in LDS; longer requests re-read scores
-
 // Wave-wide inclusive scans in lane order through DPP moves, with no LDS round trip: shifts by 1,
 // 2, 4 and 8 lanes within each row of 16, then the row totals carried forward by the broadcasts of
 // lane 15 (into rows 1 and 3) and lane 31 (into rows 2 and 3).  A lane that a move leaves without
@@ -958,8 +957,6 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t x) {
   return wave_last(wave_scan_bits(x, 0u, [](uint32_t a, uint32_t b) { return max(a, b); }));
 }
 
-constexpr int kRegKeys = kMaxLdsKeys / kThreads;    // 32 pages per thread held in registers
-
 // Options of the radix selection beyond the exact one (Sec. 5.2 approximate top-k):
 //   remap 1: keys are the affine map of the candidates' [min, max] onto 32-bit fixed point,
 //            floor((s - min) * scale), scale = 4294967295 / (max - min) in fp64;
@@ -1004,10 +1001,10 @@ __device__ __forceinline__ void block_fminmax(float& mn, float& mx, float (*wave
 // items == nullptr: the request's page count from seq_lens and the page list; else items[i]
 // (capped at the row stride).
 //
-// Thread t owns the contiguous pages [t*R, t*R + R), R = ceil(P / kThreads).  Up to
-// kMaxLdsKeys pages (R <= 32) their keys stay in registers for every radix pass and for the
-// compaction; longer rows recompute the keys from the scores (L2-resident after the first read).
-__global__ __launch_bounds__(kThreads) void topk_kernel(
+// The radix selection of rows past kTwoPassMaxPages.  Thread t owns the contiguous pages
+// [t*R, t*R + R), R = ceil(P / kThreads), and every pass recomputes their keys from the scores
+// (L2-resident after the first read).
+__global__ __launch_bounds__(kThreads) void topk_long_kernel(
     const float* __restrict__ scores, int H, int ps, int r, int max_pages, int stride, int batch,
     const int32_t* __restrict__ indptr, const int32_t* __restrict__ seq_lens, const int32_t* __restrict__ items,
     const int32_t* __restrict__ budget, int n_sink, int n_local, int max_sel, const TopkOptions opt,
@@ -1034,20 +1031,6 @@ __global__ __launch_bounds__(kThreads) void topk_kernel(
   const int Kfree = all ? 0 : max(0, Ktot - nF);
   const int R = (P + kThreads - 1) / kThreads;
   const int j_lo = min(P, tid * R), n_mine = min(P, j_lo + R) - j_lo;
-  const bool in_regs = R <= kRegKeys;
-
-  // scores of the own range (registers), and the candidate mask (bit x: page j_lo + x)
-  float sv[kRegKeys];
-  uint32_t kr[kRegKeys], cand = 0;
-  if (Kfree > 0 && in_regs) {
-#pragma unroll
-    for (int x = 0; x < kRegKeys; x++) {
-      if (x < R) sv[x] = s[x < n_mine ? j_lo + x : 0];     // all loads issued before any use
-    }
-#pragma unroll
-    for (int x = 0; x < kRegKeys; x++)
-      if (x < n_mine && !is_forced(j_lo + x, P, nS, nL)) cand |= 1u << x;
-  }
 
   double rmin = 0.0, rscale = 0.0;                       // remap 1: min and scale of the affine map
   auto make_key = [&](float x) -> uint32_t {
@@ -1056,39 +1039,11 @@ __global__ __launch_bounds__(kThreads) void topk_kernel(
     // in [0, 2^32 - 1] for candidates; forced pages (never ranked) may fall outside: clamp
     return (uint32_t)fmin(fmax(floor(((double)x - rmin) * rscale), 0.0), 4294967295.0);
   };
-  // f(key) for every candidate of this thread
-  auto each_candidate = [&](auto&& f) {
-    if (in_regs) {
-#pragma unroll
-      for (int x = 0; x < kRegKeys; x++)
-        if ((cand >> x) & 1u) f(kr[x]);
-    } else {
-      for (int j = j_lo; j < j_lo + n_mine; j++)
-        if (!is_forced(j, P, nS, nL)) f(make_key(s[j]));
-    }
-  };
   // f(j, key) for every candidate of this thread
-  auto each_candidate_j = [&](auto&& f) {
-    if (in_regs) {
-#pragma unroll
-      for (int x = 0; x < kRegKeys; x++)
-        if ((cand >> x) & 1u) f(j_lo + x, kr[x]);
-    } else {
-      for (int j = j_lo; j < j_lo + n_mine; j++)
-        if (!is_forced(j, P, nS, nL)) f(j, make_key(s[j]));
-    }
+  auto each_candidate = [&](auto&& f) {
+    for (int j = j_lo; j < j_lo + n_mine; j++)
+      if (!is_forced(j, P, nS, nL)) f(j, make_key(s[j]));
   };
-  // f(j, key) for every page of this thread in ascending order (key meaningful for candidates)
-  auto each_own = [&](auto&& f) {
-    if (in_regs) {
-#pragma unroll
-      for (int x = 0; x < kRegKeys; x++)
-        if (x < n_mine) f(j_lo + x, kr[x]);
-    } else {
-      for (int j = j_lo; j < j_lo + n_mine; j++) f(j, Kfree > 0 ? make_key(s[j]) : 0u);
-    }
-  };
-
   // Radix select over the candidates' keys.  Threshold prefix: a candidate is chosen when
   // (key & pmask) > prefix, or when it equals the prefix and its rank among equals (by page
   // index; after an early stop by (h8 desc, page)) is below `remaining`.
@@ -1123,35 +1078,21 @@ __global__ __launch_bounds__(kThreads) void topk_kernel(
     if (opt.remap != 0) {
       // the candidates' score range (NaN excluded) fixes the affine map
       float fmn = INFINITY, fmx = -INFINITY;
-      if (in_regs) {
-#pragma unroll
-        for (int x = 0; x < kRegKeys; x++) {
-          if (((cand >> x) & 1u) && sv[x] == sv[x]) {
-            fmn = fminf(fmn, sv[x]);
-            fmx = fmaxf(fmx, sv[x]);
-          }
-        }
-      } else {
-        for (int j = j_lo; j < j_lo + n_mine; j++) {
-          const float x = s[j];
-          if (!is_forced(j, P, nS, nL) && x == x) {
-            fmn = fminf(fmn, x);
-            fmx = fmaxf(fmx, x);
-          }
+      for (int j = j_lo; j < j_lo + n_mine; j++) {
+        const float x = s[j];
+        if (!is_forced(j, P, nS, nL) && x == x) {
+          fmn = fminf(fmn, x);
+          fmx = fmaxf(fmx, x);
         }
       }
       block_fminmax(fmn, fmx, wave_fm);
       rmin = (double)fmn;
       rscale = fmx > fmn ? 4294967295.0 / ((double)fmx - (double)fmn) : 0.0;
     }
-    if (in_regs) {
-#pragma unroll
-      for (int x = 0; x < kRegKeys; x++) kr[x] = x < n_mine ? make_key(sv[x]) : 0u;
-    }
     // bits above the highest bit where the smallest and largest candidate key differ are
     // common to every candidate and need no pass
     uint32_t kmin = 0xffffffffu, kmax = 0u;
-    each_candidate([&](uint32_t key) {
+    each_candidate([&](int, uint32_t key) {
       kmin = min(kmin, key);
       kmax = max(kmax, key);
     });
@@ -1179,7 +1120,7 @@ __global__ __launch_bounds__(kThreads) void topk_kernel(
       const int shift = top >= 7 ? top - 7 : 0;
       const uint32_t dmask = (1u << (top - shift + 1)) - 1u;   // 1..8 bits
       hist[hb ^ 1][tid] = 0;                                   // next pass's histogram
-      each_candidate([&](uint32_t key) {
+      each_candidate([&](int, uint32_t key) {
         if ((key & pmask) == prefix) atomicAdd(&hist[hb][(key >> shift) & dmask], 1);
       });
       __syncthreads();
@@ -1196,7 +1137,7 @@ __global__ __launch_bounds__(kThreads) void topk_kernel(
         // early termination: one pass over the threshold bin's hashes (histogram hb was
         // cleared during the last pass) orders the rest at random
         hz = lowbias32(opt.seed ^ lowbias32((uint32_t)(i * H + h)));
-        each_candidate_j([&](int j, uint32_t key) {
+        each_candidate([&](int j, uint32_t key) {
           if ((key & pmask) == prefix) atomicAdd(&hist[hb][lowbias32(hz ^ (uint32_t)j) >> 24], 1);
         });
         __syncthreads();
@@ -1218,7 +1159,7 @@ __global__ __launch_bounds__(kThreads) void topk_kernel(
   };
   int n_eq = 0;
   if (Kfree > 0) {
-    each_candidate_j([&](int j, uint32_t key) { n_eq += (key & pmask) == prefix && hash_cmp(j) == 0; });
+    each_candidate([&](int j, uint32_t key) { n_eq += (key & pmask) == prefix && hash_cmp(j) == 0; });
   }
   int tot_eq;
   const int eq_rank = block_incl_scan(n_eq, wave_tot, &tot_eq) - n_eq;
@@ -1237,18 +1178,18 @@ __global__ __launch_bounds__(kThreads) void topk_kernel(
   int n_chosen = 0;
   {
     int r = eq_rank;
-    each_own([&](int j, uint32_t key) { n_chosen += chosen_at(j, key, r); });
+    for (int j = j_lo; j < j_lo + n_mine; j++) n_chosen += chosen_at(j, Kfree > 0 ? make_key(s[j]) : 0u, r);
   }
   int tot_sel;
   int pos = block_incl_scan(n_chosen, wave_tot, &tot_sel) - n_chosen;
   {
     int r = eq_rank;
-    each_own([&](int j, uint32_t key) {
-      if (chosen_at(j, key, r)) {
+    for (int j = j_lo; j < j_lo + n_mine; j++) {
+      if (chosen_at(j, Kfree > 0 ? make_key(s[j]) : 0u, r)) {
         if (pos < max_sel) out[pos] = j;
         pos++;
       }
-    });
+    }
   }
   for (int m = tot_sel + tid; m < max_sel; m += kThreads) out[m] = -1;
   if (h == 0 && tid == 0) sel_count[i] = min(tot_sel, max_sel);
@@ -1349,6 +1290,11 @@ struct SlotWords {
     const bool mine = lane_id() == x;
     lo = mine ? (uint32_t)m : lo;
     hi = mine ? (uint32_t)(m >> 32) : hi;
+  }
+  __device__ __forceinline__ void add(int x, uint64_t m) {      // into slot x's word
+    const bool mine = lane_id() == x;
+    lo |= mine ? (uint32_t)m : 0u;
+    hi |= mine ? (uint32_t)(m >> 32) : 0u;
   }
   __device__ __forceinline__ void store(uint2* words, int w, int P) const {
     const int x = lane_id();
@@ -1902,6 +1848,203 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(D > 128 ? 2 :
   write_selection<T, K>(a, s, words, w);
 }
 
+// ------------------------------------------------------------------------------------
+// The radix selection with its options (TopkOptions; the approximate top-k and the remapped keys)
+// on the same page slots.  The options define their result by 8-bit passes from the highest bit
+// in which the candidates' extreme keys differ, so the passes stay; each costs one barrier: three
+// histograms rotate (one filling, the next one cleared, the last one possibly still being read)
+// and every wave finds the threshold bin for itself.  Latency-bound like the bucketed selection.
+// Measured against 256 threads holding 32 contiguous pages each, one wave picking per pass behind a
+// second barrier: 128 rows of 6000 to 8192 scores, remapped, tau 0.2, 25.5 -> 11.3 us a call; 37 rows
+// of up to 3000 scores 19.3 -> 8.8.
+// ------------------------------------------------------------------------------------
+template <int T, int K>
+__global__ __launch_bounds__(T) void topk_radix_kernel(const SelArgs a, const TopkOptions opt) {
+  using S = SelShape<T, K>;
+  __shared__ __align__(16) int hist[3][256];
+  __shared__ uint2 words[S::kWords];              // chosen pages
+  __shared__ uint2 eq_words[S::kWords];           // pages of the tie class
+  __shared__ uint32_t mm[2][S::W];
+  const int tid = (int)threadIdx.x, lane = lane_id();
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const SelRow s = sel_row(a, (int)blockIdx.x, S::M);
+  const int P = s.P;
+  auto is_cand = [&](int j) { return !s.all && j >= s.nS && j < P - s.nL; };
+  SlotWords<T, K> sw;
+  if (s.Kfree > 0) {
+    const float* row = a.lower + ((int64_t)s.h * a.batch + s.i) * a.stride;
+    float sv[K];
+#pragma unroll
+    for (int x = 0; x < K; x++)
+      if (x * T < P) sv[x] = row[min(x * T + tid, P - 1)];       // all loads issued before any use
+    if (tid < kWave) *reinterpret_cast<int4*>(&hist[0][4 * tid]) = make_int4(0, 0, 0, 0);
+    // Threshold prefix: a candidate is chosen when (key & pmask) > prefix, or when it equals the
+    // prefix and its rank among equals (by page; after an early stop by (h8 desc, page)) is below
+    // `remaining`.
+    uint32_t key[K], kmin, kmax;
+    if (opt.remap != 0) {
+      // the candidates' score range (NaN excluded) fixes the affine map; NaN and the smallest
+      // candidate both map to 0
+      float mn = INFINITY, mx = -INFINITY;
+#pragma unroll
+      for (int x = 0; x < K; x++) {
+        if (x * T < P && is_cand(x * T + tid) && sv[x] == sv[x]) {
+          mn = fminf(mn, sv[x]);
+          mx = fmaxf(mx, sv[x]);
+        }
+      }
+      mn = wave_min_f32(mn);
+      mx = wave_max_f32(mx);
+      if (lane == 0) {
+        mm[0][w] = __float_as_uint(mn);
+        mm[1][w] = __float_as_uint(mx);
+      }
+      __syncthreads();
+#pragma unroll
+      for (int x = 0; x < S::W; x++) {
+        mn = fminf(mn, __uint_as_float(mm[0][x]));
+        mx = fmaxf(mx, __uint_as_float(mm[1][x]));
+      }
+      const double rmin = (double)mn, rscale = mx > mn ? 4294967295.0 / ((double)mx - (double)mn) : 0.0;
+      auto make_key = [&](float x) -> uint32_t {
+        if (x != x) return 0u;
+        return (uint32_t)fmin(fmax(floor(((double)x - rmin) * rscale), 0.0), 4294967295.0);
+      };
+#pragma unroll
+      for (int x = 0; x < K; x++)
+        if (x * T < P) key[x] = make_key(sv[x]);
+      kmin = 0u;
+      kmax = mx >= mn ? make_key(mx) : 0u;
+    } else {
+      kmin = 0xffffffffu;
+      kmax = 0u;
+#pragma unroll
+      for (int x = 0; x < K; x++) {
+        if (x * T < P) {
+          key[x] = float_key(sv[x]);
+          if (is_cand(x * T + tid)) {
+            kmin = min(kmin, key[x]);
+            kmax = max(kmax, key[x]);
+          }
+        }
+      }
+      kmin = wave_min_u32(kmin);
+      kmax = wave_max_u32(kmax);
+      if (lane == 0) {
+        mm[0][w] = kmin;
+        mm[1][w] = kmax;
+      }
+      __syncthreads();
+#pragma unroll
+      for (int x = 0; x < S::W; x++) {
+        kmin = min(kmin, mm[0][x]);
+        kmax = max(kmax, mm[1][x]);
+      }
+    }
+    // Every wave: the bin of histogram hb that holds the rs.remaining-th largest digit (lane l owns
+    // the bins 255 - 4l .. 252 - 4l), the count above it and its own count.
+    RadixState rs = radix_init(kmin, kmax, s.Kfree);
+    int pk[3];
+    auto pick_bin = [&](int hb) {
+      const int4 v = *reinterpret_cast<const int4*>(&hist[hb][252 - 4 * lane]);
+      const int c[4] = {v.w, v.z, v.y, v.x};
+      const int tot = (v.x + v.y) + (v.z + v.w);
+      int above = wave_incl_sum(tot) - tot, bin = -1, bin_above = 0, bin_n = 0;
+#pragma unroll
+      for (int e = 0; e < 4; e++) {
+        if (above < rs.remaining && above + c[e] >= rs.remaining) {
+          bin = 255 - 4 * lane - e;
+          bin_above = above;
+          bin_n = c[e];
+        }
+        above += c[e];
+      }
+      const int src = __builtin_ctzll(__ballot(bin >= 0));       // one lane
+      pk[0] = __builtin_amdgcn_readlane(bin, src);
+      pk[1] = __builtin_amdgcn_readlane(bin_above, src);
+      pk[2] = __builtin_amdgcn_readlane(bin_n, src);
+    };
+    int hb = 0, certain = 0;
+    int hthr = -1;                                   // stopped early: hash threshold h8
+    const uint32_t hz = lowbias32(opt.seed ^ lowbias32((uint32_t)(s.i * a.H + s.h)));
+    auto h8 = [&](int j) { return (int)(lowbias32(hz ^ (uint32_t)j) >> 24); };
+    bool whole = false;                              // the whole tie class is chosen
+    while (rs.top >= 0) {                            // uniform
+      const int sh = radix_shift<8>(rs), nb = hb == 2 ? 0 : hb + 1;
+      const uint32_t dm = radix_dmask<8>(rs);
+      if (tid < kWave) *reinterpret_cast<int4*>(&hist[nb][4 * tid]) = make_int4(0, 0, 0, 0);
+#pragma unroll
+      for (int x = 0; x < K; x++)
+        if (x * T < P && is_cand(x * T + tid) && (key[x] & rs.pmask) == rs.prefix)
+          atomicAdd(&hist[hb][(key[x] >> sh) & dm], 1);
+      __syncthreads();
+      pick_bin(hb);
+      radix_advance<8>(rs, pk);
+      certain += pk[1];
+      whole = pk[2] == rs.remaining;
+      if (whole) break;
+      hb = nb;
+      if (rs.top >= 0 && (int64_t)certain * 65536 >= (int64_t)(65536 - opt.tau_q) * s.Kfree) {
+        // early termination: one pass over the threshold bin's hashes orders the rest at random
+#pragma unroll
+        for (int x = 0; x < K; x++) {
+          const int j = x * T + tid;
+          if (x * T < P && is_cand(j) && (key[x] & rs.pmask) == rs.prefix) atomicAdd(&hist[hb][h8(j)], 1);
+        }
+        __syncthreads();
+        pick_bin(hb);
+        rs.remaining -= pk[1];
+        hthr = pk[0];
+        whole = pk[2] == rs.remaining;
+        break;
+      }
+    }
+    SlotWords<T, K> ew;
+#pragma unroll
+    for (int x = 0; x < K; x++) {
+      if (x * T < P) {
+        const int j = x * T + tid;
+        const bool cand = is_cand(j);
+        const uint32_t mk = key[x] & rs.pmask;
+        bool eq = cand && mk == rs.prefix, in = cand && mk > rs.prefix;
+        if (hthr >= 0) {                             // uniform
+          const int hv = h8(j);
+          in = in || (eq && hv > hthr);
+          eq = eq && hv == hthr;
+        }
+        sw.put(x, __ballot(in || (whole && eq) || (j < P && !cand)));
+        ew.put(x, __ballot(eq));
+      }
+    }
+    if (!whole) {                                    // the tie class's `remaining` lowest pages
+      ew.store(eq_words, w, P);
+      __syncthreads();
+      WordPrefix<T, K> ep;
+      ep.load(eq_words, (P + T - 1) / T * S::W);
+#pragma unroll
+      for (int x = 0; x < K; x++) {
+        if (x * T < P) {
+          int rank;
+          const bool e = ep.at(x, w, rank);
+          sw.add(x, __ballot(e && rank < rs.remaining));
+        }
+      }
+    }
+  } else {
+    // every page, or the forced pages alone
+#pragma unroll
+    for (int x = 0; x < K; x++) {
+      if (x * T < P) {
+        const int j = x * T + tid;
+        sw.put(x, __ballot(j < P && !is_cand(j)));
+      }
+    }
+  }
+  sw.store(words, w, P);
+  __syncthreads();
+  write_selection<T, K>(a, s, words, w);
+}
+
 // The same exact one-pass selection for requests of at most kWaveMaxPages blocks, by one wave per
 // (request, KV head) and without workgroup barriers: lane l holds the score keys of blocks
 // 8l .. 8l + 7, an MSB-first radix select over 8-bit digits (a 256-bin LDS histogram per pass,
@@ -2221,6 +2364,33 @@ void launch_bucket(const SelArgs& a, const AppendStep& ap, hipStream_t stream) {
   }
 }
 
+// The radix selection's shape, as the bucketed one's.
+template <int T, int K>
+void launch_radix_shape(const SelArgs& a, const TopkOptions& opt, hipStream_t stream) {
+  hipLaunchKernelGGL((topk_radix_kernel<T, K>), dim3(a.batch * a.H), dim3(T), 0, stream, a, opt);
+}
+void launch_radix(const SelArgs& a, const TopkOptions& opt, hipStream_t stream) {
+  const long long pairs = (long long)a.batch * a.H, cus = device_cus();
+  if (a.max_pages <= 1024) launch_radix_shape<256, 4>(a, opt, stream);
+  else if (a.max_pages <= 2048 && pairs <= 2 * cus) launch_radix_shape<512, 4>(a, opt, stream);
+  else if (a.max_pages <= 4096 && 2 * pairs <= cus) launch_radix_shape<1024, 4>(a, opt, stream);
+  else if (a.max_pages <= 4096 && pairs <= 2 * cus) launch_radix_shape<512, 8>(a, opt, stream);
+  else if (a.max_pages <= 4096) launch_radix_shape<256, 16>(a, opt, stream);
+  else if (a.max_pages <= 8192) launch_radix_shape<1024, 8>(a, opt, stream);
+  else launch_radix_shape<1024, 16>(a, opt, stream);
+}
+
+// Selection from scores in a.lower: exact and unmapped by the bucketed kernel, else by radix
+// passes; rows past the page slots of both by the general radix kernel.
+void launch_select(const SelArgs& a, const TopkOptions& opt, const AppendStep& ap, hipStream_t stream) {
+  if (a.max_pages > kTwoPassMaxPages)
+    hipLaunchKernelGGL(topk_long_kernel, dim3(a.batch * a.H), dim3(kThreads), 0, stream, a.lower, a.H, a.ps, a.r,
+                       a.max_pages, a.stride, a.batch, a.indptr, a.seq_lens, a.items, a.budget, a.n_sink, a.n_local,
+                       a.max_sel, opt, a.sel_pages, a.sel_count);
+  else if (opt.remap != 0 || opt.tau_q != 0) launch_radix(a, opt, stream);
+  else launch_bucket<kNoRescore, 0>(a, ap, stream);
+}
+
 }  // namespace
 
 int device_cus() {
@@ -2401,13 +2571,7 @@ hipError_t launch_score_topk(const Geometry& g, const uint16_t* q, int Hq, int k
                        max_sel, sel_pages, sel_count, ap);
     return hipGetLastError();
   }
-  if (g.max_pages <= kTwoPassMaxPages && !approx) {
-    launch_bucket<kNoRescore, 0>(t, ap, stream);
-    return hipGetLastError();
-  }
-  hipLaunchKernelGGL(topk_kernel, dim3(g.batch * g.H), dim3(kThreads), 0, stream, scores, g.H, g.bs, g.r,
-                     g.max_pages, a.stride, g.batch, g.indptr, g.seq_lens, nullptr, budget, n_sink, n_local, max_sel,
-                     TopkOptions{remap, tau_q, seed}, sel_pages, sel_count);
+  launch_select(t, TopkOptions{remap, tau_q, seed}, ap, stream);
   return hipGetLastError();
 }
 
@@ -2454,9 +2618,21 @@ hipError_t launch_topk_select(const float* scores, int stride, int H, int batch,
                               const int32_t* budget, int n_sink, int n_local, int max_sel, int remap, int tau_q,
                               uint32_t seed, int32_t* sel_pages, int32_t* sel_count, hipStream_t stream) {
   if (batch == 0) return hipSuccess;
-  hipLaunchKernelGGL(topk_kernel, dim3(batch * H), dim3(kThreads), 0, stream, scores, H, 16, 1, stride, stride, batch,
-                     nullptr, nullptr, items, budget, n_sink, n_local, max_sel, TopkOptions{remap, tau_q, seed},
-                     sel_pages, sel_count);
+  SelArgs t{};
+  t.lower = t.upper = scores;
+  t.Hq = t.H = H;
+  t.ps = 16;
+  t.r = 1;
+  t.max_pages = t.stride = stride;
+  t.batch = batch;
+  t.items = items;
+  t.budget = budget;
+  t.n_sink = n_sink;
+  t.n_local = n_local;
+  t.max_sel = max_sel;
+  t.sel_pages = sel_pages;
+  t.sel_count = sel_count;
+  launch_select(t, TopkOptions{remap, tau_q, seed}, AppendStep{}, stream);
   return hipGetLastError();
 }
 

@@ -71,3 +71,27 @@ def test_selection_shapes(kind, two_pass, P, B, H, dist):
     o_sel, o_cnt = O.topk_select(scores.float().numpy(), pages, budget, 1, 3 if max_sel > 4 else 0, max_sel)
     assert (cnt == o_cnt).all()
     assert (sel == o_sel).all()
+
+
+@pytest.mark.parametrize("dist", ["normal", "equal", "skewed", "coarse"])
+@pytest.mark.parametrize("tau,remap", [(0.0, 0), (0.0, 1), (0.2, 0), (0.2, 1)])
+@pytest.mark.parametrize("P,B,H", [(1, 2, 1), (500, 3, 2), (1025, 3, 2), (2048, 40, 16), (2049, 2, 2), (4096, 5, 4),
+                                   (4096, 33, 16), (4097, 3, 2), (8193, 2, 1), (16384, 2, 1), (16385, 2, 1)])
+def test_radix_selection_shapes(P, B, H, tau, remap, dist):
+    """vx_topk_select at the same edges, its options included, over rows of any alignment."""
+    rng = np.random.default_rng(P + B)
+    x = _scores((H, B, P), dist, rng).float()
+    if P > 1 and dist == "normal":
+        x[:, 0, P // 3] = float("nan")
+    items = rng.integers(P // 2, P + 1, B).astype(np.int32)
+    items[0] = P
+    budget = rng.integers(1, max(2, P // 2), B).astype(np.int32)
+    max_sel = int(budget.max()) + 4
+    sel = torch.full((B, H, max_sel), -7, dtype=torch.int32, device="cuda")
+    cnt = torch.full((B,), -7, dtype=torch.int32, device="cuda")
+    vx.topk_select(x.cuda().contiguous(), torch.from_numpy(items).cuda(), torch.from_numpy(budget).cuda(), 1, 2, max_sel,
+                   sel, cnt, tolerate_ratio=tau, seed=5, remap=remap)
+    torch.cuda.synchronize()
+    o_sel, o_cnt = O.topk_select(x.numpy(), items, budget, 1, 2, max_sel, tau=tau, seed=5, remap=remap)
+    assert (cnt.cpu().numpy() == o_cnt).all()
+    assert (sel.cpu().numpy() == o_sel).all()
