@@ -21,11 +21,26 @@ __device__ __forceinline__ float quad_dpp(float x) {
   return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), CTRL, 0xf, 0xf, false));
 }
 
+// 16 bytes to dst, with the non-temporal hint when STREAM.
+template <bool STREAM, class V>
+__device__ __forceinline__ void put16(void* dst, V v) {
+  const u32x4_t w = __builtin_bit_cast(u32x4_t, v);
+  if constexpr (STREAM) __builtin_nontemporal_store(w, reinterpret_cast<u32x4_t*>(dst));
+  else *reinterpret_cast<u32x4_t*>(dst) = w;
+}
+
 // 8 consecutive channels of one token row: raw bits and their fp32 values.
 template <int KT>
 struct RowChunk {
   using Raw = typename std::conditional<KT == kKvBf16, uint4, uint2>::type;
   static constexpr int kBytes = KT == kKvBf16 ? 16 : 8;
+  // STREAM: with the non-temporal hint
+  template <bool STREAM>
+  __device__ static __forceinline__ Raw load(const char* p) {
+    if constexpr (!STREAM) return *reinterpret_cast<const Raw*>(p);
+    else if constexpr (KT == kKvBf16) return load_stream_u4(p);
+    else return load_stream_u2(p);
+  }
   __device__ static __forceinline__ void values(const Raw& w, float scale, float (&x)[8]) {
     if constexpr (KT == kKvBf16) {
       const uint32_t ws[4] = {w.x, w.y, w.z, w.w};
@@ -66,7 +81,9 @@ struct AppendArgs {
 
 // Task (block j of request i, KV head h, channel chunk c8); `active` false: the lane only joins
 // the quad's DPP exchanges.  Block j is block j % r of the page at indices[base + j / r].
-template <int TS, int KT, bool APPEND, int KB = kBatch>
+// MEAN, ENV: whether the task forms the Mean and the Max / Min at all (a false one's outputs are
+// null).
+template <int TS, int KT, bool APPEND, int KB = kBatch, bool MEAN = true, bool ENV = true>
 __device__ __forceinline__ void task(const void* __restrict__ kv, float k_scale, int num_phys, int H, int ps, int bs,
                                      int r, int D, const int32_t* __restrict__ indices, int base, int L, int i, int j,
                                      int h, int c8, bool active, int slice, float* __restrict__ mean,
@@ -76,6 +93,8 @@ __device__ __forceinline__ void task(const void* __restrict__ kv, float k_scale,
   // a sum (the compiler could fuse it in one launch's copy of this code and not in another's,
   // and the summaries of the append and of a pass over the page would then differ).
 #pragma clang fp contract(off)
+  // a full pass (one lane per task) streams: neither the keys nor the summaries are read again soon
+  constexpr bool kFull = TS == 1;
   const int64_t p = clamp_page(indices[base + j / r], num_phys);
   const int blk = j - (j / r) * r;                    // block within the page
   const int n = active ? min(bs, L - j * bs) : 0;
@@ -109,23 +128,29 @@ __device__ __forceinline__ void task(const void* __restrict__ kv, float k_scale,
     typename RC::Raw w[KB];
 #pragma unroll
     for (int b = 0; b < KB; b++)
-      w[b] = *reinterpret_cast<const typename RC::Raw*>(src + (int64_t)min(t0 + TS * b, n_mem - 1) * row_bytes);
+      w[b] = RC::template load<kFull>(src + (int64_t)min(t0 + TS * b, n_mem - 1) * row_bytes);
     // The rows past the block's end are masked instead of skipped: a branch per row would let the
     // compiler sink each load into it, one round trip per row.  Adding +0 leaves s unchanged (s
     // starts at +0 and round-to-nearest never makes it -0), and -inf / +inf leave the max / min
     // unchanged, so the sums are those of the valid rows in the same order.
+    auto add_rows = [&](auto masked) {
 #pragma unroll
-    for (int b = 0; b < KB; b++) {
-      const bool ok = t0 + TS * b < n_mem;
-      float x[8];
-      RC::values(w[b], k_scale, x);
+      for (int b = 0; b < KB; b++) {
+        const bool ok = !decltype(masked)::value || t0 + TS * b < n_mem;
+        float x[8];
+        RC::values(w[b], k_scale, x);
 #pragma unroll
-      for (int e = 0; e < 8; e++) {
-        s[e] += ok ? x[e] : 0.f;
-        mx[e] = fmaxf(mx[e], ok ? x[e] : -INFINITY);
-        mn[e] = fminf(mn[e], ok ? x[e] : INFINITY);
+        for (int e = 0; e < 8; e++) {
+          if constexpr (MEAN) s[e] += ok ? x[e] : 0.f;
+          if constexpr (ENV) {
+            mx[e] = fmaxf(mx[e], ok ? x[e] : -INFINITY);
+            mn[e] = fminf(mn[e], ok ? x[e] : INFINITY);
+          }
+        }
       }
-    }
+    };
+    if (t0 + TS * (KB - 1) < n_mem) add_rows(std::false_type{});
+    else add_rows(std::true_type{});
   }
   if constexpr (APPEND) {
     if (writer) {
@@ -160,14 +185,14 @@ __device__ __forceinline__ void task(const void* __restrict__ kv, float k_scale,
   }
   if (!active || slice != 0) return;
   const int64_t o = ((p * r + blk) * H + h) * (int64_t)D + c8 * 8;
-  if (mean || mean_bf) {
+  if (MEAN && (mean || mean_bf)) {
     const float nf = (float)n;   // correctly rounded division below
     float m8[8];
 #pragma unroll
     for (int e = 0; e < 8; e++) m8[e] = s[e] / nf;
     if (mean) {
-      *reinterpret_cast<float4*>(mean + o) = make_float4(m8[0], m8[1], m8[2], m8[3]);
-      *reinterpret_cast<float4*>(mean + o + 4) = make_float4(m8[4], m8[5], m8[6], m8[7]);
+      put16<kFull>(mean + o, make_float4(m8[0], m8[1], m8[2], m8[3]));
+      put16<kFull>(mean + o + 4, make_float4(m8[4], m8[5], m8[6], m8[7]));
     }
     if (mean_bf) {
       uint4 w;
@@ -175,7 +200,7 @@ __device__ __forceinline__ void task(const void* __restrict__ kv, float k_scale,
       w.y = f32_to_bf16_rne(m8[2]) | (f32_to_bf16_rne(m8[3]) << 16);
       w.z = f32_to_bf16_rne(m8[4]) | (f32_to_bf16_rne(m8[5]) << 16);
       w.w = f32_to_bf16_rne(m8[6]) | (f32_to_bf16_rne(m8[7]) << 16);
-      *reinterpret_cast<uint4*>(mean_bf + o) = w;
+      put16<kFull>(mean_bf + o, w);
     }
   }
   // Max and Min of bf16 values are bf16 values: truncating the fp32 bits is exact.  Those
@@ -184,13 +209,13 @@ __device__ __forceinline__ void task(const void* __restrict__ kv, float k_scale,
     if constexpr (KT == kKvBf16) return (__float_as_uint(a) >> 16) | (__float_as_uint(b) & 0xffff0000u);
     else return f32_to_bf16_rne(a) | (f32_to_bf16_rne(b) << 16);
   };
-  if (maxo) {
-    *reinterpret_cast<uint4*>(maxo + o) = make_uint4(pack(mx[0], mx[1]), pack(mx[2], mx[3]), pack(mx[4], mx[5]),
-                                                     pack(mx[6], mx[7]));
+  if (ENV && maxo) {
+    put16<kFull>(maxo + o, make_uint4(pack(mx[0], mx[1]), pack(mx[2], mx[3]), pack(mx[4], mx[5]),
+                                      pack(mx[6], mx[7])));
   }
-  if (mino) {
-    *reinterpret_cast<uint4*>(mino + o) = make_uint4(pack(mn[0], mn[1]), pack(mn[2], mn[3]), pack(mn[4], mn[5]),
-                                                     pack(mn[6], mn[7]));
+  if (ENV && mino) {
+    put16<kFull>(mino + o, make_uint4(pack(mn[0], mn[1]), pack(mn[2], mn[3]), pack(mn[4], mn[5]),
+                                      pack(mn[6], mn[7])));
   }
 }
 
