@@ -38,7 +38,8 @@ constexpr int kRows = kThreads / 16;     // 16-lane rows per workgroup
 //   kQuestConsensus  min over heads of sum_c max(q Max, q Min)   (head-consensus Quest)
 //   kEnvLower        max over heads of sum_c min(q Max, q Min)   (pessimistic envelope)
 //   kQuestRectified  max over heads of sum_c ReLU(q Max)         (rectified Quest)
-// kHeadDot is the first step of the NSA flow: one logit q_r . Mean per query head.
+// kHeadDot is the first step of the NSA flow, one logit q_r . Mean per query head (its own kernel,
+// head_score_kernel).
 // kQuestBound .. kRectifiedBound are the first passes of the exact two-pass selection for the
 // four envelope kinds: fp32 sums of the exact products with a rigorous bound, an interval that
 // holds the one-pass score.
@@ -67,11 +68,11 @@ constexpr bool needs_min(int k) {
   return k == kQuest || k == kQuestConsensus || k == kEnvLower || k == kQuestBound || k == kConsensusBound ||
          k == kEnvLowerBound;
 }
-constexpr bool per_head(int k) { return is_env(k) || is_env_bound(k) || k == kHeadDot; }
+constexpr bool per_head(int k) { return is_env(k) || is_env_bound(k); }
 // Kinds whose scores table holds a lower and an upper plane.
 constexpr bool has_bounds(int k) { return k == kMeanBound || is_env_bound(k); }
 // Kinds that read fp32 Mean rows.
-constexpr bool reads_mean(int k) { return k == kMeanDot || k == kHeadDot; }
+constexpr bool reads_mean(int k) { return k == kMeanDot; }
 // Internal kind of an ABI score kind.
 constexpr int internal_kind(int abi) {
   return abi <= 2 ? abi : abi <= 5 ? abi + 1 : abi == kAbiNsa ? kHeadDot : kMeanDot;
@@ -412,68 +413,15 @@ struct ScorePolicy {
     uint32_t a[U][W];                     // Mean / Max rows
     uint32_t b[needs_min(KIND) ? U : 1][needs_min(KIND) ? W : 1];   // Min rows
   };
-  // kHeadDot with groups of 1, 2 or 4 query heads and D <= 128 keeps the row's channels of the
-  // group's query heads in registers as fp64 (the other geometries read them from LDS per item)
-  static constexpr bool kHeadRegs = KIND == kHeadDot && D <= 128;
   double qb[KIND == kMeanBound || per_head(KIND) ? 1 : E];  // the row's channels of qbar (exact, fp64)
   float qf[KIND == kMeanBound ? E : 1];   // kMeanBound: the same channels rounded to fp32
   float qabs;                             // kMeanBound: sum over the row of |qf_c|
-  double qh[kHeadRegs ? 4 : 1][kHeadRegs ? E : 1];
   // bound kinds: the row's channels of the group's (at most four) query heads as packed bf16
   // pairs split by sign (qp: the channels with q >= 0, the others zero; qn: those with q < 0),
   // zero for heads past g, and the 1-norm over all D channels of this lane's head u / 4
   static constexpr bool kBound = is_env_bound(KIND);
   uint32_t qp[kBound ? 4 : 1][kBound ? E / 2 : 1], qn[kBound ? 4 : 1][kBound ? E / 2 : 1];
   float qnorm;
-
-  static __device__ __forceinline__ bool head_regs(int g) { return kHeadRegs && (g == 1 || g == 2 || g == 4); }
-
-  // kHeadDot: the row's channels of query heads h g + r (qs: the request's query block in LDS,
-  // fp32 in row order), exact as fp64.
-  __device__ __forceinline__ void on_new_request_heads(const float* qs, int h, int g, int u) {
-    if constexpr (kHeadRegs) {
-      if (!head_regs(g)) return;
-#pragma unroll
-      for (int r = 0; r < 4; r++)
-#pragma unroll
-        for (int e = 0; e < E; e++) qh[r][e] = r < g ? (double)qs[((h * g + r) * 16 + u) * E + e] : 0.0;
-    }
-  }
-
-  // kHeadDot, G = g query heads per KV head: the G logits z_r = q_r . Mean of one item from
-  // registers.  Each lane forms its G partial sums (fp64 products, exact), then the row
-  // reduces them with a reduce-scatter: at each of the first log2(G) levels a lane keeps half
-  // of its heads and adds its partner's half (row rotation by 8, then the half-row mirror), and
-  // the lanes left holding the same head sum their partials over the quad.  Lanes 16/G apart
-  // then hold the G totals; one of each writes its logit, rounded once to fp32.
-  template <int G>
-  __device__ __forceinline__ void head_logits(const uint32_t (&w)[W], int h, int u, int jj, float* __restrict__ out,
-                                              int64_t plane) const {
-    double p[G];
-#pragma unroll
-    for (int r = 0; r < G; r++) p[r] = 0.0;
-#pragma unroll
-    for (int e = 0; e < E; e++) {
-      const double m = (double)row_value<D, false>(w, e);
-#pragma unroll
-      for (int r = 0; r < G; r++) p[r] = fma(qh[r][e], m, p[r]);
-    }
-    double z;
-    if constexpr (G == 1) {
-      z = row16_sum_f64(p[0]);
-    } else if constexpr (G == 4) {
-      z = reduce_scatter4(p, u);
-    } else {
-      const bool up = (u & 8) != 0;                // lanes u and u ^ 8 keep one head each
-      const double s = up ? p[0] : p[1];
-      z = (up ? p[1] : p[0]) + dpp_f64<0x128>(s);
-      z += dpp_f64<0x141>(z);                      // lanes u and 7 - u of the half row
-      z += dpp_f64<0x4E>(z);                       // quad lanes u ^ 2
-      z += dpp_f64<0xB1>(z);                       // quad lanes u ^ 1
-    }
-    constexpr int span = 16 / G;                   // lanes holding one head's total
-    if (u % span == 0) out[(int64_t)(h * (G - 1) + u / span) * plane + jj] = (float)z;
-  }
 
   // Bound kinds: the row's query registers and the head norms (qs: the request's query block in
   // LDS, fp32 in row order; g <= 4).
@@ -548,8 +496,6 @@ struct ScorePolicy {
 
   // Scores of the stage's items; lane v of the row keeps item v's score, and one store per
   // plane writes them all: out[jj] (and, for the bounds, the upper one at out[plane + jj]).
-  // kHeadDot writes one logit per query head r of the group instead, lane r storing it to
-  // out[(h (g - 1) + r) plane + jj], the row of query head h g + r.
   __device__ __forceinline__ void compute(const Stage& st, const float* qs, int h, int g, int u, int j0, int slots,
                                           int nj, float* __restrict__ out, int64_t plane) const {
     float mine = 0.f, mine_up = 0.f;
@@ -637,25 +583,6 @@ struct ScorePolicy {
             mine_up = hi;
           }
           continue;
-        } else if constexpr (KIND == kHeadDot) {
-          if constexpr (kHeadRegs) {
-            if (g == 4) { head_logits<4>(st.a[v], h, u, jj, out, plane); continue; }
-            if (g == 2) { head_logits<2>(st.a[v], h, u, jj, out, plane); continue; }
-            if (g == 1) { head_logits<1>(st.a[v], h, u, jj, out, plane); continue; }
-          }
-          // z_r = q_r . Mean: fp64 products (q is a bf16 value held in fp32) and sums, one
-          // rounding to fp32
-          double mine_z = 0.0;
-          for (int r = 0; r < g; r++) {
-            const float* qr = qs + ((h * g + r) * 16 + u) * E;
-            double acc = 0.0;
-#pragma unroll
-            for (int e = 0; e < E; e++) acc = fma((double)qr[e], (double)row_value<D, false>(st.a[v], e), acc);
-            acc = row16_sum_f64(acc);
-            if (u == r) mine_z = acc;
-          }
-          if (u < g) out[(int64_t)(h * (g - 1) + u) * plane + jj] = (float)mine_z;
-          continue;
         } else if constexpr (KIND == kMeanBound) {
           // In fp32: s' = qf . m and A' = sum |qf_c| |m_c| with m = bf16(Mean) and qf = fp32(qbar).
           // The exact score s (fp64 products of qbar and the fp32 Mean, one rounding to fp32)
@@ -692,11 +619,9 @@ struct ScorePolicy {
       }
     }
     const int jj = j0 + u * slots;
-    if constexpr (KIND != kHeadDot) {
-      if (u < U && jj < nj) {
-        out[jj] = mine;
-        if constexpr (has_bounds(KIND)) out[plane + jj] = mine_up;
-      }
+    if (u < U && jj < nj) {
+      out[jj] = mine;
+      if constexpr (has_bounds(KIND)) out[plane + jj] = mine_up;
     }
   }
 };
@@ -832,7 +757,6 @@ __global__ __launch_bounds__(kThreads) void score_kernel(const ScoreArgs a) {
     if (ci != cur_req && cn > 0) {                       // uniform over the block; qraw holds ci's block
       if constexpr (per_head(KIND)) {
         convert_query<D, P::kBf16>(qraw, a.Hq, qs);
-        if constexpr (KIND == kHeadDot) pol.on_new_request_heads(qs, h, g, u);
         if constexpr (is_env_bound(KIND)) pol.on_new_request_bound(qs, h, g, u);
       } else {
         finish_qbar<D>(qraw, a.Hq, a.H, a.qdims, qbar);
@@ -881,6 +805,201 @@ __global__ __launch_bounds__(kThreads) void score_kernel(const ScoreArgs a) {
     if (ni != raw_req) {                                 // uniform over the block
       load_query_raw(a.q, ni, n8, none, qraw);
       raw_req = ni;
+    }
+    buf ^= 1;
+    ci = ni;
+    ck = nk;
+    cn = nn;
+    cj = nj0;
+    cend = nend;
+  }
+}
+
+// ------------------------------------------------------------------------------------
+// Per-query-head logits z_r = q_r . Mean_j (the NSA flow's first step): fp64 products and sums, one
+// rounding to fp32, on the fp64 matrix cores.  The walk over the batch's page references is
+// score_kernel's.  v_mfma_f64_4x4x4 multiplies four 4x4 blocks; here a wave takes four pages of
+// one KV head (A rows i = lane & 3), four query heads of its group (B columns j = lane & 3) and
+// splits the channels over k = lane >> 4 and the blocks b = (lane >> 2) & 3: a lane loads the
+// 16-byte chunks 4k + b + 16c of its page's Mean row, one channel of which enters each MFMA, and the
+// four blocks' sums meet in two DPP additions.  Groups of more than four heads take NS sets of four.
+// The query takes 2 D/16 registers a set instead of four times as many per lane of a 16-lane row,
+// and the row reductions fall away, so four waves fit per SIMD where the VALU form ran at two.
+// KV heads: wave w of a workgroup takes H / 4 adjacent heads of H >= 4, one after the other over
+// each stage's pages, so that a page's rows are read close together in time; with fewer heads the
+// waves of one head share out the pages.
+// Bound: the fp32 Mean stream.  Measured (64 requests of 8192 to 32768 tokens, 8 KV heads, groups of
+// four, 325 MB), VALU form 84 us: one head at a time over a whole chunk of pages 87 us, heads w and
+// w + 4 over each stage 74, adjacent heads 69 (4.7 TB/s).  Without the stores 8 us less; without the
+// matrix instructions 2 us less; with cached instead of non-temporal loads 78.
+template <int D, int NS, bool LDS_IND>
+__global__ __launch_bounds__(kThreads)
+    __attribute__((amdgpu_waves_per_eu(NS == 1 ? 4 : NS == 2 ? 3 : 2))) void head_score_kernel(const ScoreArgs a) {
+  constexpr int C = D / 64;                // 16-byte chunks of a row per lane
+  constexpr int U = 8 / C;                 // pages per lane and stage: 128 bytes of loads
+  constexpr int E = 4 * C;                 // channels per lane
+  __shared__ int pid[2][kChunk];
+  extern __shared__ uint4 dyn_lds[];
+  const int B = a.batch, tid = (int)threadIdx.x, lane = lane_id();
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int i = lane & 3, b = (lane >> 2) & 3, k = lane >> 4;
+  const int n8 = a.Hq * D / 8, g = a.Hq / a.H;
+  uint4* qraw = dyn_lds;                   // two query blocks: the current chunk's and the next one's
+  int* ind_lds = reinterpret_cast<int*>(dyn_lds + 2 * n8);
+  if constexpr (LDS_IND) {
+    for (int x = tid; x <= B; x += kThreads) ind_lds[x] = a.indptr[x];
+    for (int x = tid; x < B; x += kThreads) ind_lds[B + 1 + x] = a.seq_lens[x];
+  }
+  __syncthreads();
+  auto ind = [&](int x) -> int { return (LDS_IND ? ind_lds[x] : a.indptr[x]) * a.r; };
+  auto len = [&](int x) -> int { return LDS_IND ? ind_lds[B + 1 + x] : a.seq_lens[x]; };
+  int k0, k1;
+  {
+    const int n = ind(B), prog = (int)blockIdx.x, nprog = (int)gridDim.x;
+    const int per = n / nprog, rem = n % nprog;
+    k0 = prog * per + min(prog, rem);
+    k1 = k0 + per + (prog < rem ? 1 : 0);
+  }
+  if (k0 >= k1) return;                    // uniform over the workgroup
+  int lo = 0, hi = B - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (ind(mid) <= k0) lo = mid;
+    else hi = mid - 1;
+  }
+  auto advance = [&](int& x, int kk) {
+    while (x < B - 1 && ind(x + 1) <= kk) x++;
+    return min(k1, min(kk + kChunk, ind(x + 1)));
+  };
+  auto pages_in = [&](int x, int kk, int end, int& j0) {
+    const int base = ind(x);
+    const int P = num_pages(len(x), a.ps, ind(x + 1) - base, a.max_pages);
+    j0 = kk - base;
+    return max(0, min(end, base + P) - kk);
+  };
+  // the wave's heads and its share of a chunk's pages
+  const int passes = a.H >= 4 ? a.H / 4 : 1, slots = a.H >= 4 ? 4 : 16 / a.H;
+  const int h0 = a.H >= 4 ? w * passes : w % a.H, slot0 = a.H >= 4 ? 0 : 4 * (w / a.H);
+
+  QueryPrefetch none;
+  int ci = lo, ck = k0, cend = advance(ci, ck), cj;
+  if (tid < cend - ck) pid[0][tid] = (int)block_row(a.indices, ck + tid, a.r, a.num_phys);
+  load_query_raw(a.q, ci, n8, none, qraw);
+  int cn = pages_in(ci, ck, cend, cj);
+  int buf = 0, qb = 0, next_raw = 0;
+  uint4 sa[U][C], sb[U][C];
+  double qv[NS][E];
+  while (true) {
+    __syncthreads();                       // pid[buf] and the query block ready
+    const int* pc = pid[buf];
+    // stage (pass, j0): pages j0 + i + slots v of the pass's head
+    auto load = [&](int pass, int j0, uint4 (&st)[U][C]) {
+      const int h = h0 + pass;
+#pragma unroll
+      for (int v = 0; v < U; v++) {
+        if (j0 + v * slots >= cn) continue;                        // uniform over the wave
+        const int j = min(j0 + v * slots + i, cn - 1);
+        const float* src = a.mean + ((int64_t)pc[j] * a.H + h) * D + 4 * (4 * k + b);
+#pragma unroll
+        for (int c = 0; c < C; c++) st[v][c] = load_stream_u4(src + 64 * c);
+      }
+    };
+    auto load_q = [&](int pass) {
+      const int h = h0 + pass;
+      const uint16_t* qh = reinterpret_cast<const uint16_t*>(qraw + qb * n8);
+#pragma unroll
+      for (int s = 0; s < NS; s++) {
+        const int r = 4 * s + i;                                   // column j of B: query head 4 s + j
+        const bool ok = r < g;
+#pragma unroll
+        for (int c = 0; c < C; c++) {
+          const uint2 x = *reinterpret_cast<const uint2*>(qh + (h * g + (ok ? r : 0)) * D + 64 * c + 4 * (4 * k + b));
+          qv[s][4 * c] = ok ? (double)bf16lo(x.x) : 0.0;
+          qv[s][4 * c + 1] = ok ? (double)bf16hi(x.x) : 0.0;
+          qv[s][4 * c + 2] = ok ? (double)bf16lo(x.y) : 0.0;
+          qv[s][4 * c + 3] = ok ? (double)bf16hi(x.y) : 0.0;
+        }
+      }
+    };
+    auto compute = [&](int pass, int j0, const uint4 (&st)[U][C]) {
+      // D row i, column j of block b sits in lane 16 i + 4 b + j
+      const int jd = lane & 3, id = lane >> 4, bd = b;
+      float mine = 0.f;
+#pragma unroll
+      for (int p = 0; p < U * NS; p++) {
+        const int v = p / NS, s = p % NS;
+        if (j0 + v * slots < cn) {
+          double acc = 0.0;
+#pragma unroll
+          for (int c = 0; c < C; c++) {
+            acc = __builtin_amdgcn_mfma_f64_4x4x4f64((double)__uint_as_float(st[v][c].x), qv[s][4 * c], acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f64_4x4x4f64((double)__uint_as_float(st[v][c].y), qv[s][4 * c + 1], acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f64_4x4x4f64((double)__uint_as_float(st[v][c].z), qv[s][4 * c + 2], acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f64_4x4x4f64((double)__uint_as_float(st[v][c].w), qv[s][4 * c + 3], acc, 0, 0, 0);
+          }
+          acc += dpp_f64<0x128>(acc);                              // blocks b ^ 2, then b ^ 1 (row rotations)
+          acc += dpp_f64<0x124>(acc);
+          if (bd == p % 4) mine = (float)acc;
+        }
+        if (p % 4 == 3) {
+          // lane (i, b, j) holds sum p - 3 + b: its page and head, one store for four sums
+          const int pp = p - 3 + bd, pv = pp / NS, r = 4 * (pp % NS) + jd;
+          const int jj = j0 + pv * slots + id, h = h0 + pass;
+          if (r < g && jj < cn) a.scores[(int64_t)(h * g + r) * a.plane + (int64_t)ci * a.stride + cj + jj] = mine;
+        }
+      }
+    };
+    static_assert(U * NS % 4 == 0, "whole stores");
+    auto step = [&](int& pass, int& j0) {  // the next stage; false past the last
+      if (++pass == passes) {
+        pass = 0;
+        j0 += U * slots;
+      }
+      return j0 < cn;
+    };
+    int pa = 0, ja = slot0;
+    const bool active = slot0 < cn;
+    if (active) {
+      load(pa, ja, sa);
+      load_q(0);
+    }
+    // next chunk: its end, and its raw page ids into a register, consumed after this chunk's work
+    int ni = ci, nk = cend, nend = cend;
+    const bool more = nk < k1;
+    if (more) {
+      nend = advance(ni, nk);
+      if (tid < nend - nk) next_raw = a.indices[(nk + tid) / a.r];
+    }
+    if (active) {
+      int pb = pa, jb = ja;
+      while (true) {
+        bool go = step(pb, jb);
+        if (go) load(pb, jb, sb);
+        compute(pa, ja, sa);
+        if (!go) break;
+        if (pb != pa) load_q(pb);
+        pa = pb;
+        ja = jb;
+        go = step(pa, ja);
+        if (go) load(pa, ja, sa);
+        compute(pb, jb, sb);
+        if (!go) break;
+        if (pa != pb) load_q(pa);
+        pb = pa;
+        jb = ja;
+      }
+    }
+    if (!more) break;
+    int nj0;
+    const int nn = pages_in(ni, nk, nend, nj0);
+    asm volatile("" : "+v"(next_raw));     // the load completes here, on every lane, not in a branch
+    if (tid < nn) {
+      const int jb = nk + tid, q = jb / a.r;
+      pid[buf ^ 1][tid] = (int)(clamp_page(next_raw, a.num_phys) * a.r + (jb - q * a.r));
+    }
+    if (ni != ci) {                        // uniform: the next request's block, beside the one in use
+      qb ^= 1;
+      load_query_raw(a.q, ni, n8, none, qraw + qb * n8);
     }
     buf ^= 1;
     ci = ni;
@@ -2182,44 +2301,44 @@ __global__ __launch_bounds__(kWave) void topk_wave_kernel(
 // KV head), in fp64 with one rounding to fp32:
 //   NSA (its block top-k flow, Sec. 3.2: softmax, convolution, head sum, then top-K): for each query
 //     head r of the group, p_rj = exp(z_rj - m_r) / l_r, the softmax over the request's pages of
-//     the fp32 logits z_r (m_r their max, l_r = sum_j exp(z_rj - m_r); rows of up to
-//     kFlowStaged pages multiply by the fp64 reciprocal of l_r); then the conv below; then the
-//     sum over the group's heads, in head order.
+//     the fp32 logits z_r (m_r their max, l_r = sum_j exp(z_rj - m_r), divided through the fp64
+//     reciprocal of l_r); then the conv below; then the sum over the group's heads, in head order.
 //   positional smoothing (Appendix G): the conv of the block-mean scores.
 // Conv1d along the pages with taps (1/4, 1/2, 1/4) and zero padding:
 //   y_j = x_{j-1} / 4 + x_j / 2 + x_{j+1} / 4,  x_{-1} = x_P = 0.
 // in: [rows][batch][stride] (NSA: a row per query head; smoothing: a row per KV head).
 // out: [H][batch][stride].
 // ------------------------------------------------------------------------------------
-constexpr int kFlowStaged = 2048;    // NSA rows up to this many pages keep their exponentials in LDS
+constexpr int kFlowTile = 2048;      // pages of a row whose exponentials are in LDS at a time
 
 __device__ __forceinline__ double conv3(double left, double mid, double right) {
   return 0.25 * left + 0.5 * mid + 0.25 * right;
 }
 
-__device__ __forceinline__ double block_sum_f64(double x, double* red) {
-  const int lane = lane_id(), w = threadIdx.x >> 6;
-#pragma unroll
-  for (int off = kWave / 2; off > 0; off >>= 1) x += __shfl_xor(x, off, kWave);
-  __syncthreads();                                   // red free from its previous use
-  if (lane == 0) red[w] = x;
-  __syncthreads();
-  double t = 0.0;
-#pragma unroll
-  for (int k = 0; k < kThreads / kWave; k++) t += red[k];
-  return t;
+// Sum over the wave; every lane receives it.
+__device__ __forceinline__ double wave_sum_f64(double x) {
+  x = row16_sum_f64(x);
+  x += __shfl_xor(x, 16, kWave);
+  x += __shfl_xor(x, 32, kWave);
+  return x;
 }
 
+// NSA: wave w takes the query heads w, w + 4, ... of the group by itself, so a head's max and sum
+// are wave reductions; the exponentials of four heads (a row of up to kFlowTile pages, longer rows
+// tile by tile, with the two neighbours) meet in LDS, where every thread convolves and sums its
+// pages' heads.  Two barriers per four heads where one workgroup per head row needed six each: the
+// kernel waits on its chain of barriers and fp64 exponentials.  Measured (64 requests of 8192 to 32768
+// tokens on pages of 16, 8 KV heads, groups of four): 24.2 -> 13.6 us.
 template <bool kNsa>
 __global__ __launch_bounds__(kThreads) void flow_kernel(const float* __restrict__ in, float* __restrict__ out, int H,
                                                         int g, int ps, int r, int max_pages, int stride, int batch,
                                                         const int32_t* __restrict__ indptr,
                                                         const int32_t* __restrict__ seq_lens,
                                                         const int32_t* __restrict__ items) {
-  __shared__ double red[kThreads / kWave];
-  __shared__ float wave_fm[2][kThreads / kWave];
-  __shared__ double m_of[16], l_of[16];
-  __shared__ double e_lds[kNsa ? kFlowStaged : 1];  // exp(z_j - m) of one head's row
+  constexpr int W = kThreads / kWave;
+  extern __shared__ double e_lds[];                  // NSA: [W][row], row = tile + 2: e_j at 1 + j - tile start
+  __shared__ double inv_of[16];
+  __shared__ float max_of[16];
   const int tid = threadIdx.x;
   const int i = blockIdx.x / H, h = blockIdx.x % H;
   const int P = items ? max(0, min(items[i], stride))
@@ -2234,69 +2353,86 @@ __global__ __launch_bounds__(kThreads) void flow_kernel(const float* __restrict_
     }
     return;
   }
-  if (P <= kFlowStaged) {
-    // rows up to kFlowStaged pages: one exponential per page and head, staged in LDS for the
-    // convolution's neighbours; thread t accumulates pages t, t + kThreads, ... in registers
-    double acc[kFlowStaged / kThreads];
-#pragma unroll
-    for (int k = 0; k < kFlowStaged / kThreads; k++) acc[k] = 0.0;
-    for (int r = 0; r < g; r++) {
-      const float* z = in + ((int64_t)(h * g + r) * batch + i) * stride;
-      float mx = -INFINITY, mn = INFINITY;
-      for (int j = tid; j < P; j += kThreads) mx = fmaxf(mx, z[j]);
-      __syncthreads();                               // wave_fm and e_lds free from their last use
-      block_fminmax(mn, mx, wave_fm);
+  const int lane = lane_id(), w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int tile = min(max_pages, kFlowTile), row = tile + 2;
+  double* e = e_lds + w * row;
+  const bool staged = P <= tile;                     // uniform: one tile, its sums taken on the way
+  auto logits = [&](int rr) { return in + ((int64_t)(h * g + rr) * batch + i) * stride; };
+  if (!staged) {
+    for (int rr = w; rr < g; rr += W) {
+      const float* z = logits(rr);
+      float mx = -INFINITY;
+      for (int j = lane; j < P; j += kWave) mx = fmaxf(mx, z[j]);
+      mx = wave_max_f32(mx);
       double l = 0.0;
-      for (int j = tid; j < P; j += kThreads) {
-        const double e = exp((double)z[j] - (double)mx);
-        e_lds[j] = e;
-        l += e;
+      for (int j = lane; j < P; j += kWave) l += exp((double)z[j] - (double)mx);
+      l = wave_sum_f64(l);
+      if (lane == 0) {
+        max_of[rr] = mx;
+        inv_of[rr] = 1.0 / l;
       }
-      l = block_sum_f64(l, red);                     // its barriers also publish e_lds
-      const double inv_l = 1.0 / l;
-      for (int j = tid; j < P; j += kThreads) e_lds[j] *= inv_l;   // the softmax of the row
+    }
+    __syncthreads();
+  }
+  for (int t0 = 0; t0 < P; t0 += tile) {
+    const int t1 = min(P, t0 + tile);
+    double acc[kFlowTile / kThreads];
+#pragma unroll
+    for (int x = 0; x < kFlowTile / kThreads; x++) acc[x] = 0.0;
+    for (int r0 = 0; r0 < g; r0 += W) {
+      const int rr = r0 + w;
+      if (rr < g) {                                  // uniform over the wave
+        const float* z = logits(rr);
+        if (staged) {
+          float zr[kFlowTile / kWave];
+          float mx = -INFINITY;
+#pragma unroll
+          for (int x = 0; x < kFlowTile / kWave; x++)
+            if (x * kWave < P) zr[x] = z[min(x * kWave + lane, P - 1)];   // one round trip
+#pragma unroll
+          for (int x = 0; x < kFlowTile / kWave; x++)
+            if (x * kWave < P) mx = fmaxf(mx, zr[x]);
+          mx = wave_max_f32(mx);
+          double l = 0.0;
+#pragma unroll
+          for (int x = 0; x < kFlowTile / kWave; x++) {
+            if (x * kWave < P) {
+              const int j = x * kWave + lane;
+              const double v = exp((double)zr[x] - (double)mx);
+              if (j < P) {
+                e[1 + j] = v;
+                l += v;
+              }
+            }
+          }
+          l = wave_sum_f64(l);
+          if (lane == 0) inv_of[rr] = 1.0 / l;
+        } else {
+          const double mx = (double)max_of[rr];
+          for (int j = max(0, t0 - 1) + lane; j < min(P, t1 + 1); j += kWave) e[1 + j - t0] = exp((double)z[j] - mx);
+        }
+        if (lane == 0) {                             // zero padding at the ends of the row
+          if (t0 == 0) e[0] = 0.0;
+          if (t1 == P) e[1 + P - t0] = 0.0;
+        }
+      }
       __syncthreads();
+      const int n = min(W, g - r0);
 #pragma unroll
-      for (int k = 0; k < kFlowStaged / kThreads; k++) {
-        const int j = tid + k * kThreads;
-        if (j < P) acc[k] += conv3(j > 0 ? e_lds[j - 1] : 0.0, e_lds[j], j + 1 < P ? e_lds[j + 1] : 0.0);
+      for (int x = 0; x < kFlowTile / kThreads; x++) {
+        const int j = t0 + x * kThreads + tid;
+        if (j < t1) {
+          const double* q = e_lds + 1 + j - t0;
+          for (int s = 0; s < n; s++, q += row) acc[x] += conv3(q[-1], q[0], q[1]) * inv_of[r0 + s];
+        }
       }
+      __syncthreads();                               // e free for the next heads or tile
     }
 #pragma unroll
-    for (int k = 0; k < kFlowStaged / kThreads; k++) {
-      const int j = tid + k * kThreads;
-      if (j < P) y[j] = (float)acc[k];
+    for (int x = 0; x < kFlowTile / kThreads; x++) {
+      const int j = t0 + x * kThreads + tid;
+      if (j < t1) y[j] = (float)acc[x];
     }
-    return;
-  }
-  // longer rows: softmax statistics of each query head's row, then three exponentials per
-  // page and head (the neighbours are recomputed rather than staged)
-  for (int r = 0; r < g; r++) {
-    const float* z = in + ((int64_t)(h * g + r) * batch + i) * stride;
-    float mx = -INFINITY, mn = INFINITY;
-    for (int j = tid; j < P; j += kThreads) mx = fmaxf(mx, z[j]);
-    __syncthreads();                                 // wave_fm free from its previous use
-    block_fminmax(mn, mx, wave_fm);
-    double l = 0.0;
-    for (int j = tid; j < P; j += kThreads) l += exp((double)z[j] - (double)mx);
-    l = block_sum_f64(l, red);
-    if (tid == 0) {
-      m_of[r] = (double)mx;
-      l_of[r] = l;
-    }
-  }
-  __syncthreads();
-  for (int j = tid; j < P; j += kThreads) {
-    double acc = 0.0;
-    for (int r = 0; r < g; r++) {
-      const float* z = in + ((int64_t)(h * g + r) * batch + i) * stride;
-      const double m = m_of[r], l = l_of[r];
-      const double left = j > 0 ? exp((double)z[j - 1] - m) / l : 0.0;
-      const double mid = exp((double)z[j] - m) / l;
-      const double right = j + 1 < P ? exp((double)z[j + 1] - m) / l : 0.0;
-      acc += conv3(left, mid, right);
-    }
-    y[j] = (float)acc;
   }
 }
 
@@ -2307,13 +2443,7 @@ __global__ __launch_bounds__(kThreads) void flow_kernel(const float* __restrict_
 // Measured on the MLA workload (16384 items; score + top-K): 30.0 us with every resident slot,
 // 25.1 us at 32 items per workgroup, 27.1 us at 64 and 27.0 us at 128.
 constexpr int kMinItemsPerWg = 32;
-template <int KIND, int D>
-void launch_score(const ScoreArgs& a, hipStream_t stream) {
-  const size_t lds = (size_t)score_lds<KIND, D>(a.batch, a.Hq, a.H).total;
-  // page_indptr in LDS up to kMaxLdsBatch requests, read from global memory beyond
-  const bool lds_ind = a.batch <= kMaxLdsBatch;
-  const void* fn = lds_ind ? reinterpret_cast<const void*>(score_kernel<KIND, D, true>)
-                           : reinterpret_cast<const void*>(score_kernel<KIND, D, false>);
+int score_grid(const void* fn, size_t lds, const ScoreArgs& a) {
   int per_cu = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, kThreads, lds) != hipSuccess || per_cu < 1)
     per_cu = 1;
@@ -2326,9 +2456,35 @@ void launch_score(const ScoreArgs& a, hipStream_t stream) {
   const int cus = device_cus();
   const long long items = (long long)a.batch * a.max_pages * a.H;
   const long long by_items = (items + kMinItemsPerWg - 1) / kMinItemsPerWg;
-  const long long grid = std::max<long long>(cus, std::min<long long>((long long)per_cu * cus * kScoreGridFactor, by_items));
-  if (lds_ind) hipLaunchKernelGGL((score_kernel<KIND, D, true>), dim3((unsigned)grid), dim3(kThreads), lds, stream, a);
-  else hipLaunchKernelGGL((score_kernel<KIND, D, false>), dim3((unsigned)grid), dim3(kThreads), lds, stream, a);
+  return (int)std::max<long long>(cus, std::min<long long>((long long)per_cu * cus * kScoreGridFactor, by_items));
+}
+template <int KIND, int D>
+void launch_score(const ScoreArgs& a, hipStream_t stream) {
+  const size_t lds = (size_t)score_lds<KIND, D>(a.batch, a.Hq, a.H).total;
+  // page_indptr in LDS up to kMaxLdsBatch requests, read from global memory beyond
+  const bool lds_ind = a.batch <= kMaxLdsBatch;
+  const void* fn = lds_ind ? reinterpret_cast<const void*>(score_kernel<KIND, D, true>)
+                           : reinterpret_cast<const void*>(score_kernel<KIND, D, false>);
+  const int grid = score_grid(fn, lds, a);
+  if (lds_ind) hipLaunchKernelGGL((score_kernel<KIND, D, true>), dim3(grid), dim3(kThreads), lds, stream, a);
+  else hipLaunchKernelGGL((score_kernel<KIND, D, false>), dim3(grid), dim3(kThreads), lds, stream, a);
+}
+template <int D, int NS>
+void launch_head_score_sets(const ScoreArgs& a, hipStream_t stream) {
+  const bool lds_ind = a.batch <= kMaxLdsBatch;
+  const size_t lds = (size_t)2 * a.Hq * D * 2 + (lds_ind ? (size_t)(2 * a.batch + 1) * 4 : 0);
+  const void* fn = lds_ind ? reinterpret_cast<const void*>(head_score_kernel<D, NS, true>)
+                           : reinterpret_cast<const void*>(head_score_kernel<D, NS, false>);
+  const int grid = score_grid(fn, lds, a);
+  if (lds_ind) hipLaunchKernelGGL((head_score_kernel<D, NS, true>), dim3(grid), dim3(kThreads), lds, stream, a);
+  else hipLaunchKernelGGL((head_score_kernel<D, NS, false>), dim3(grid), dim3(kThreads), lds, stream, a);
+}
+template <int D>
+void launch_head_score(const ScoreArgs& a, hipStream_t stream) {
+  const int g = a.Hq / a.H;
+  if (g <= 4) launch_head_score_sets<D, 1>(a, stream);
+  else if (g <= 8) launch_head_score_sets<D, 2>(a, stream);
+  else launch_head_score_sets<D, 4>(a, stream);
 }
 
 // The bucketed selection's shape: as many threads as keep a request's pages at four slots each
@@ -2426,7 +2582,10 @@ void launch_one_pass_score(int abi_kind, int Dqk, const ScoreArgs& a, hipStream_
     case kQuestConsensus: VX_ENV(kQuestConsensus); break;
     case kEnvLower: VX_ENV(kEnvLower); break;
     case kQuestRectified: VX_ENV(kQuestRectified); break;
-    case kHeadDot: VX_ENV(kHeadDot); break;
+    case kHeadDot:
+      if (Dqk == 64) launch_head_score<64>(a, stream);
+      else launch_head_score<128>(a, stream);
+      break;
     default: VX_ENV(kMaxDot); break;
   }
 #undef VX_ENV
@@ -2606,8 +2765,9 @@ hipError_t launch_score_flow(int kind, const float* in, float* out, int stride, 
                              const int32_t* seq_lens, hipStream_t stream) {
   if (batch == 0) return hipSuccess;
   if (kind == kAbiNsa)
-    hipLaunchKernelGGL(flow_kernel<true>, dim3(batch * H), dim3(kThreads), 0, stream, in, out, H, Hq / H, ps, r,
-                       max_pages, stride, batch, indptr, seq_lens, items);
+    hipLaunchKernelGGL(flow_kernel<true>, dim3(batch * H), dim3(kThreads),
+                       sizeof(double) * (kThreads / kWave) * (std::min(max_pages, kFlowTile) + 2), stream, in, out, H,
+                       Hq / H, ps, r, max_pages, stride, batch, indptr, seq_lens, items);
   else
     hipLaunchKernelGGL(flow_kernel<false>, dim3(batch * H), dim3(kThreads), 0, stream, in, out, H, Hq / H, ps, r,
                        max_pages, stride, batch, indptr, seq_lens, items);

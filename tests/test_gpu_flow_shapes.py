@@ -1,0 +1,60 @@
+"""The NSA flow at the edges of its kernels: groups that fill one, two and four sets of four matrix
+columns and leave some empty, KV head counts above and below the waves of a workgroup, rows around the
+pages that the flow stages at once, blocks below the page size."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import oracle as O
+from paper_2606_06453_amd import vx
+from tests._problems import random_problem
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("D,H,g", [(64, 1, 1), (128, 1, 5), (64, 2, 4), (128, 2, 16), (128, 4, 3), (64, 8, 8),
+                                   (128, 8, 9), (128, 16, 2), (64, 16, 13)])
+@pytest.mark.parametrize("block", [0, 16])
+def test_head_logits(D, H, g, block):
+    ps = 32
+    pb = random_problem(31 * D + H + g, [ps * 70 + 3, 5, ps * 9, 1], Hq=H * g, H=H, D=D, ps=ps, extra_pages=3)
+    kv = vx.PagedKV(pb.k.cuda(), pb.v.cuda(), D, block_size=block)
+    bs = block or ps
+    pages = (pb.seq_lens + ps - 1) // ps
+    batch = vx.BatchSpec(torch.from_numpy(pb.page_indptr).cuda(), torch.from_numpy(pb.page_indices).cuda(),
+                         torch.from_numpy(pb.seq_lens).cuda(), int(pages.max()))
+    mean = torch.zeros((pb.k.shape[0] * ps // bs, H, D), dtype=torch.float32, device="cuda")
+    vx.page_summarize(kv, batch, None, mean)
+    stride = int(pages.max()) * (ps // bs) + 1
+    z = torch.full((H * g, pb.batch, stride), float("nan"), device="cuda")
+    vx.page_score(pb.q.cuda(), kv, batch, vx.NSA, mean, None, None, z)
+    torch.cuda.synchronize()
+    got, m, q = z.cpu().numpy(), mean.cpu().double().numpy(), pb.q.double().numpy()
+    for i in range(pb.batch):
+        n = -(-int(pb.seq_lens[i]) // bs)
+        phys = pb.page_indices[pb.page_indptr[i]:pb.page_indptr[i + 1]]
+        rows = (phys[:, None] * (ps // bs) + np.arange(ps // bs)).reshape(-1)[:n]
+        ref = np.einsum("hgd,phd->hgp", q[i].reshape(H, g, D), m[rows]).reshape(H * g, n)
+        # fp64 sums of exact products, one rounding to fp32
+        assert np.abs(got[:, i, :n] - ref).max() <= 2.0 ** -24 * np.abs(ref).max() * (1 + 2.0 ** -20)
+        assert np.isnan(got[:, i, n:]).all()
+
+
+@pytest.mark.parametrize("g", [1, 3, 4, 5, 16])
+@pytest.mark.parametrize("P", [1, 63, 65, 2047, 2048, 2049, 4096, 4099])
+def test_nsa_flow_rows(P, g):
+    H, B = 2, 2
+    n = np.array([P, max(1, P // 2)], np.int32)
+    rng = np.random.default_rng(P + g)
+    z = (6.0 * rng.standard_normal((H * g, B, P))).astype(np.float32)
+    out = torch.full((H, B, P), float("nan"), device="cuda")
+    vx.score_flow(vx.NSA, torch.from_numpy(z).cuda(), out, H, torch.from_numpy(n).cuda())
+    torch.cuda.synchronize()
+    indptr = np.concatenate([[0], np.cumsum(n)]).astype(np.int32)
+    ragged = np.concatenate([z[:, i, :n[i]].T for i in range(B)]).astype(np.float64)
+    ref = O.nsa_scores(ragged, H, 16, indptr, (n * 16).astype(np.int32))
+    got = out.cpu().numpy().astype(np.float64)
+    for i in range(B):
+        r = ref[indptr[i]:indptr[i + 1]].T
+        assert (np.abs(got[:, i, :n[i]] - r) <= 2.0 ** -23 * np.abs(r) + 1e-30).all()
+        assert np.isnan(got[:, i, n[i]:]).all()
