@@ -36,7 +36,7 @@ namespace {
 constexpr int kThreads = 256;
 using summ::AppendArgs;
 
-template <int TS, int KT, bool APPEND, int KB, bool MEAN, bool ENV>
+template <int TS, int KT, bool APPEND, int KB, bool MEAN, bool ENV, bool STREAM>
 __global__ __launch_bounds__(kThreads) void summarize_kernel(
     const void* __restrict__ kv, float k_scale, int num_phys, int H, int ps, int bs, int r, int D, int max_pages,
     const int32_t* __restrict__ indptr, const int32_t* __restrict__ indices,
@@ -77,8 +77,8 @@ __global__ __launch_bounds__(kThreads) void summarize_kernel(
       const int h = rem / chunks;
       const int c8 = rem - h * chunks;
       const int j = jb + jj;                              // logical block
-      summ::task<TS, KT, APPEND, KB, MEAN, ENV>(kv, k_scale, num_phys, H, ps, bs, r, D, indices, base, L, i, j, h, c8,
-                                                active, slice, mean, mean_bf, maxo, mino, app);
+      summ::task<TS, KT, APPEND, KB, MEAN, ENV, STREAM>(kv, k_scale, num_phys, H, ps, bs, r, D, indices, base, L, i, j,
+                                                        h, c8, active, slice, mean, mean_bf, maxo, mino, app);
     }
   }
 }
@@ -90,11 +90,12 @@ int step_wgs(const Geometry& g) {
   return (tasks_per_page + kThreads / 4 - 1) / (kThreads / 4);
 }
 
-template <int TS, bool APPEND = false, int KB = summ::kBatch, bool MEAN = true, bool ENV = true>
+template <int TS, bool APPEND = false, int KB = summ::kBatch, bool MEAN = true, bool ENV = true,
+          bool STREAM = TS == 1>
 void dispatch(const Geometry& g, const int32_t* first_page, float* mean, uint16_t* mean_bf, uint16_t* maxo,
               uint16_t* mino, dim3 grid, int ppb, int split, hipStream_t stream, const AppendArgs& app = AppendArgs{}) {
 #define VX_SUMMARIZE(KT)                                                                                        \
-  hipLaunchKernelGGL((summarize_kernel<TS, KT, APPEND, KB, MEAN, ENV>), grid, dim3(kThreads), 0, stream, g.k, g.k_scale,   \
+  hipLaunchKernelGGL((summarize_kernel<TS, KT, APPEND, KB, MEAN, ENV, STREAM>), grid, dim3(kThreads), 0, stream, g.k, g.k_scale, \
                      g.num_phys_pages, g.H, g.ps, g.bs, g.r, g.Dqk, g.max_pages, g.indptr, g.indices, g.seq_lens,  \
                      first_page,                                                                                 \
                      mean, mean_bf, maxo, mino, ppb, split, app)
@@ -119,17 +120,33 @@ hipError_t launch_summarize(const Geometry& g, const int32_t* first_page, float*
     else
       dispatch<4>(g, first_page, mean, mean_bf, maxo, mino, dim3(step_wgs(g), g.batch), 1, 1, stream);
   } else {
-    const int ppb = tasks_per_page >= kThreads ? 1 : kThreads / tasks_per_page;
+    // Blocks of 16 tokens are one round trip per task.  Once a launch is many rounds of workgroups
+    // deep, two rounds of tasks per workgroup halve what each spends on its request's geometry; a
+    // small launch needs the workgroups.  At one / two rounds: 16 prompts of 16k to 32k tokens, E4M3
+    // Mean 126.1 / 118.2 us, envelope 114.1 / 108.1, bf16 187.1 / 188.8 and 182.3 / 180.0; one prompt
+    // of 4000 tokens 5.1 / 7.4; blocks of 64, E4M3 87.4 / 91.8.
+    const int ppb1 = tasks_per_page >= kThreads ? 1 : kThreads / tasks_per_page;
+    const long long wgs = ((long long)g.max_pages + ppb1 - 1) / ppb1 * g.batch;
+    const bool two = g.kv_dtype != kKvBf16 && g.bs <= 16 && tasks_per_page <= kThreads && wgs >= 32LL * device_cus();
+    const int ppb = two ? 2 * ppb1 : ppb1;
     int gx = (g.max_pages + ppb - 1) / ppb;
     if (gx < 1) gx = 1;
     // a score kind reads the Mean or the Max / Min, so most callers ask for one of the two
     const dim3 grid(gx, g.batch);
     constexpr int KB = 2 * summ::kBatch;
-    if (!maxo && !mino)
-      dispatch<1, false, KB, true, false>(g, first_page, mean, mean_bf, maxo, mino, grid, ppb, 0, stream);
-    else if (!mean && !mean_bf)
-      dispatch<1, false, KB, false, true>(g, first_page, mean, mean_bf, maxo, mino, grid, ppb, 0, stream);
-    else dispatch<1, false, KB>(g, first_page, mean, mean_bf, maxo, mino, grid, ppb, 0, stream);
+    auto pass = [&](auto stream_loads) {
+      constexpr bool S = decltype(stream_loads)::value;
+      if (!maxo && !mino)
+        dispatch<1, false, KB, true, false, S>(g, first_page, mean, mean_bf, maxo, mino, grid, ppb, 0, stream);
+      else if (!mean && !mean_bf)
+        dispatch<1, false, KB, false, true, S>(g, first_page, mean, mean_bf, maxo, mino, grid, ppb, 0, stream);
+      else dispatch<1, false, KB, true, true, S>(g, first_page, mean, mean_bf, maxo, mino, grid, ppb, 0, stream);
+    };
+    // A token row shorter than a cache line (fp8 at 64 channels) shares its line with the next row's
+    // load, which the non-temporal hint may fetch again: 32 prompts of 8k to 32k tokens, 2 KV heads,
+    // E4M3 Mean 33.6 us with the hint, 30.9 without; with whole lines (128 channels) 126.1 / 129.9.
+    if (g.Dqk * (g.kv_dtype == kKvBf16 ? 2 : 1) < 128) pass(std::false_type{});
+    else pass(std::true_type{});
   }
   return hipGetLastError();
 }

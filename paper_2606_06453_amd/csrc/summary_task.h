@@ -82,8 +82,8 @@ struct AppendArgs {
 // Task (block j of request i, KV head h, channel chunk c8); `active` false: the lane only joins
 // the quad's DPP exchanges.  Block j is block j % r of the page at indices[base + j / r].
 // MEAN, ENV: whether the task forms the Mean and the Max / Min at all (a false one's outputs are
-// null).
-template <int TS, int KT, bool APPEND, int KB = kBatch, bool MEAN = true, bool ENV = true>
+// null).  STREAM: the token rows' loads take the non-temporal hint.
+template <int TS, int KT, bool APPEND, int KB = kBatch, bool MEAN = true, bool ENV = true, bool STREAM = TS == 1>
 __device__ __forceinline__ void task(const void* __restrict__ kv, float k_scale, int num_phys, int H, int ps, int bs,
                                      int r, int D, const int32_t* __restrict__ indices, int base, int L, int i, int j,
                                      int h, int c8, bool active, int slice, float* __restrict__ mean,
@@ -128,7 +128,7 @@ __device__ __forceinline__ void task(const void* __restrict__ kv, float k_scale,
     typename RC::Raw w[KB];
 #pragma unroll
     for (int b = 0; b < KB; b++)
-      w[b] = RC::template load<kFull>(src + (int64_t)min(t0 + TS * b, n_mem - 1) * row_bytes);
+      w[b] = RC::template load<STREAM>(src + (int64_t)min(t0 + TS * b, n_mem - 1) * row_bytes);
     // The rows past the block's end are masked instead of skipped: a branch per row would let the
     // compiler sink each load into it, one round trip per row.  Adding +0 leaves s unchanged (s
     // starts at +0 and round-to-nearest never makes it -0), and -inf / +inf leave the max / min
