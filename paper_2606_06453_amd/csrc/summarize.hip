@@ -121,13 +121,14 @@ hipError_t launch_summarize(const Geometry& g, const int32_t* first_page, float*
       dispatch<4>(g, first_page, mean, mean_bf, maxo, mino, dim3(step_wgs(g), g.batch), 1, 1, stream);
   } else {
     // Blocks of 16 tokens are one round trip per task.  Once a launch is many rounds of workgroups
-    // deep, two rounds of tasks per workgroup halve what each spends on its request's geometry; a
-    // small launch needs the workgroups.  At one / two rounds: 16 prompts of 16k to 32k tokens, E4M3
-    // Mean 126.1 / 118.2 us, envelope 114.1 / 108.1, bf16 187.1 / 188.8 and 182.3 / 180.0; one prompt
-    // of 4000 tokens 5.1 / 7.4; blocks of 64, E4M3 87.4 / 91.8.
+    // deep, two rounds of tasks per workgroup halve what each spends on its request's geometry (and
+    // the workgroups past the ends of short requests); a small launch needs the workgroups, and a
+    // bf16 Mean's stores keep them busy.  At one / two rounds: 16 prompts of 16k to 32k tokens, E4M3
+    // Mean 127.1 / 118.5 us, envelope 115.0 / 109.0, bf16 Max 174.2 / 170.5, envelope 182.7 / 180.8,
+    // Mean 188.3 / 190.2; one prompt of 4000 tokens 5.1 / 7.4; blocks of 64, E4M3 89.0 / 93.9.
     const int ppb1 = tasks_per_page >= kThreads ? 1 : kThreads / tasks_per_page;
     const long long wgs = ((long long)g.max_pages + ppb1 - 1) / ppb1 * g.batch;
-    const bool two = g.kv_dtype != kKvBf16 && g.bs <= 16 && tasks_per_page <= kThreads && wgs >= 32LL * device_cus();
+    const bool two = g.bs <= 16 && (g.kv_dtype != kKvBf16 || (!mean && !mean_bf)) && wgs >= 32LL * device_cus();
     const int ppb = two ? 2 * ppb1 : ppb1;
     int gx = (g.max_pages + ppb - 1) / ppb;
     if (gx < 1) gx = 1;

@@ -1,5 +1,5 @@
 """Full summary passes at the launch shapes they choose between: one and two rounds of tasks per
-workgroup (fp8 blocks of 16 tokens under a large request bound), token rows below and of a cache line,
+workgroup (blocks of 16 tokens under a large request bound), token rows below and of a cache line,
 the Mean alone, the envelope alone and both, ragged last blocks and an empty request."""
 import pytest
 import torch
