@@ -529,9 +529,10 @@ struct ScorePolicy {
           // 2^-126 per step over the row, which (|q_h|_1 + m) 2^-110 + 2^-110 covers.  So every
           // head's one-pass sum lies in [s_h - b, s_h + b].  The max (min) over the heads of the
           // ends then brackets the one-pass score, before and after its rounding to fp32
-          // (monotone).  m is taken on the bf16 bit patterns (magnitudes order as integers); an
-          // item with an infinite or NaN Max / Min gets the interval (-inf, inf), so its exact
-          // score decides.
+          // (monotone).  m is taken on the bf16 bit patterns (magnitudes order as integers).  A head
+          // whose terms could leave the fp32 range, an infinite or NaN operand included (b then is
+          // infinite, NaN or at least 2^100, and the fp32 sum may be NaN where the fp64 one is an
+          // ordinary number), gets the interval (-inf, inf), so the exact score decides.
           float ax[4] = {0.f, 0.f, 0.f, 0.f}, ay[4] = {0.f, 0.f, 0.f, 0.f};
           uint32_t mb = 0u;
 #pragma unroll
@@ -562,8 +563,8 @@ struct ScorePolicy {
           const float z = reduce_scatter4(acc, u);           // lane u: head u / 4
           const uint32_t mbits = row16_max_u32(max(mb << 16, mb & 0xffff0000u));
           const float m = __uint_as_float(mbits);
-          const bool finite = mbits < 0x7f800000u;             // uniform over the row
           const float b = qnorm * m * 0x1p-18f + (qnorm + m) * 0x1p-110f + 0x1p-110f;
+          const bool finite = b < 0x1p100f;
           constexpr float kNone = KIND == kConsensusBound ? INFINITY : -INFINITY;
           float lo = (u >> 2) < g ? (finite ? z - b : -INFINITY) : kNone;
           float hi = (u >> 2) < g ? (finite ? z + b : INFINITY) : kNone;
@@ -596,7 +597,9 @@ struct ScorePolicy {
           //             any fp32 bound on the fp64 value)
           // with A = sum |qbar_c m_c| <= A' (1 + 2^-18).  b = A' (2^-8 + 2^-16) covers all of
           // these plus the fp32 rounding of s' -/+ b itself (at most u (|s'| + b) <= 2^-23 A');
-          // 2^-120 covers products that underflow.  So L = s' - b <= s <= s' + b = U.
+          // 2^-120 covers products that underflow.  So L = s' - b <= s <= s' + b = U.  Where A' is
+          // infinite, NaN or near the end of the fp32 range, s' may be NaN while s is an ordinary
+          // number: the interval is (-inf, inf) and the exact score decides.
           float acc = 0.f, aab = 0.f;
 #pragma unroll
           for (int e = 0; e < E; e++) {
@@ -607,9 +610,10 @@ struct ScorePolicy {
           acc = row16_sum_f32(acc);
           aab = row16_sum_f32(aab);
           const float b = aab * (0x1p-8f + 0x1p-16f) + qabs * 0x1p-133f + 0x1p-120f;
+          const bool finite = b < 0x1p100f;
           if (u == v) {
-            mine = acc - b;
-            mine_up = acc + b;
+            mine = finite ? acc - b : -INFINITY;
+            mine_up = finite ? acc + b : INFINITY;
           }
           continue;
         } else {
