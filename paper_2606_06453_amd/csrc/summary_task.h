@@ -149,7 +149,11 @@ __device__ __forceinline__ void task(const void* __restrict__ kv, float k_scale,
         }
       }
     };
-    if (t0 + TS * (KB - 1) < n_mem) add_rows(std::false_type{});
+    // A full pass has whole batches to add unmasked; in the step's kernels, whose blocks are mostly
+    // part full, a second copy of the rows only takes registers (one-wave selection 135 -> 196, step
+    // refresh of blocks of 64 fp8 rows 106 -> 180, two waves per SIMD: the refresh of 512 requests'
+    // blocks of 16 heads 21.4 -> 32.1 us, an MLA selection of 128 requests with its append 28.1 -> 29.9).
+    if (kFull && t0 + TS * (KB - 1) < n_mem) add_rows(std::false_type{});
     else add_rows(std::true_type{});
   }
   if constexpr (APPEND) {
