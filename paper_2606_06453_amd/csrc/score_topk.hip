@@ -1489,7 +1489,8 @@ constexpr int kBins = 1024;            // histogram bins: 16 per lane of the wav
 // entries above it and its own count, in pick[0..2].  Lane l owns the bins 1023 - 16 l .. 1008 - 16 l.
 __device__ __forceinline__ void wave_pick_bin(const int* hist, int k, int* pick) {
   constexpr int N = kBins / kWave;
-  const int lane = lane_id();
+  int lane = lane_id();
+  asm volatile("" : "+v"(lane));                     // the bin numbers stay here, not in registers around a loop
   int c[N], tot = 0;
 #pragma unroll
   for (int e = 0; e < N; e += 4) {
@@ -1573,9 +1574,16 @@ __device__ __forceinline__ void append_tasks(const AppendStep& ap, int a, int H,
 //   B(lower) > T_hi  -> in:  at most K candidates, itself included, can score >= it;
 //   otherwise undecided: ranked by its exact score; the best K - |in| of them by (score desc,
 //   page asc) complete the set.
-// B is non-decreasing, so the classification is as rigorous on bins as on the floats.  One pass
-// of kBins bins leaves at most a few pages per bin at the threshold for up to 16 pages per bin of
-// spread-out scores; finer bins would not narrow the bounds.
+// B is non-decreasing, so the classification is as rigorous on bins as on the floats.  kBins bins are
+// enough for the block mean, whose bounds span about nine of them on spread-out scores; the envelope
+// bounds are some 25 times narrower than a bin, which then leaves the two to six pages that share
+// the threshold's, and one block that scores far above the others widens the bins for all.  So
+// while both thresholds lie in one bin or in neighbours and more pages are undecided than one round of
+// re-scoring takes, the undecided are binned again, between the extremes of the thresholds' own bins.
+// Whole call, 64 pairs of 8192 blocks, one block scaled by 1 / 300 / 10^6: Quest 63.4 / 85.0 / 305 us with
+// one histogram, 63.7 / 72.3 / 82 so; block mean 39.1 / 48.9 / 176 and 39.2 / 46.7 / 57.  Refining fewer
+// pages than that costs more than re-scoring them (Quest 68.4 us without an outlier, 52.7 instead of
+// 45.9 on 16 pairs of 16384 blocks).
 // RK = kMeanDot: the two-pass block-mean selection (bounds in, fp32 Mean rows of D channels for
 // the re-scoring with exact_row_score, the one-pass arithmetic).  RK = an envelope kind: the
 // two-pass selection of that kind (bounds in, bf16 Max and Min rows of D channels for the
@@ -1583,7 +1591,10 @@ __device__ __forceinline__ void append_tasks(const AppendStep& ap, int a, int H,
 // undecided pages are ranked by their own scores.
 // Up to a wave of undecided pages is ranked by one wave; more (near-ties, or skewed scores such as
 // the NSA softmax, which put most candidates in the lowest bins) by a radix select over the exact
-// keys.  More than kMaxUndecided pages to re-score: every candidate is re-scored instead.
+// keys.  More than kMaxUndecided pages to re-score (bounds wider than the scores' spread): every page
+// is re-scored, in batches whose rows and page ids load ahead of their use.  One workgroup then reads
+// all of its row: 64 pairs of 8192 blocks whose Means differ by 2 % of their size, whole call 166 us with
+// two dependent pages per lane row at a time, 145 so; 16 pairs of 16384 blocks 306 / 228.
 // What bounds it is instruction issue (the active-instruction counter covers 8 of the 12 us on 512
 // pairs) behind a chain of five round trips: few operations per page slot matter more than their
 // latency.  Kernel trace, against 16-bit bucket keys found in two 256-bin passes by four waves of 16
@@ -1593,6 +1604,15 @@ __device__ __forceinline__ void append_tasks(const AppendStep& ap, int a, int H,
 // 5.0.
 // ------------------------------------------------------------------------------------
 constexpr int kMaxUndecided = 1024;
+constexpr int kBinRounds = 4;          // histograms of the re-scored kinds at most
+
+// Bins per unit between lo and hi, 0 for an empty or infinite range.  A finite range that overflows
+// fp32 is halved first (x - lo may then be infinite: the last bin).
+__device__ __forceinline__ float bin_scale(float lo, float hi) {
+  const float span = hi - lo;
+  if (!(span > 0.f)) return 0.f;
+  return span < INFINITY ? (float)kBins / span : (float)(kBins / 2) / (0.5f * hi - 0.5f * lo);
+}
 
 // Six waves per SIMD (80 VGPRs) where the re-scoring allows it: the registers the compiler would
 // otherwise take for the append workgroups' divisions cost the selection its residency, and a grid
@@ -1600,7 +1620,7 @@ constexpr int kMaxUndecided = 1024;
 // upsets the decode launch's pairing of long and short requests per CU (1024 pairs: decode 36.5 us
 // after a selection at four waves per SIMD, 34.2 us at six).
 template <int RK, int D, int T, int K>
-__global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(D > 128 ? 2 : K > 8 && (T > 256 || RK != kNoRescore) ? 4 : 6))) void topk_bucket_kernel(const SelArgs a, const AppendStep ap) {
+__global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(D > 128 ? 2 : (T > 512 && RK != kNoRescore) || (K > 8 && (T > 256 || RK != kNoRescore)) ? 4 : 6))) void topk_bucket_kernel(const SelArgs a, const AppendStep ap) {
   using S = SelShape<T, K>;
   constexpr bool kMeanRescore = RK == kMeanDot;
   constexpr bool kEnvRescore = is_env(RK);
@@ -1623,7 +1643,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(D > 128 ? 2 :
   __shared__ float qs[kEnvRescore ? 4 * D : 1];   // the group's query rows, fp32 in row order
   __shared__ int pick[2][3];
   __shared__ uint32_t mm[2][S::W];
-  __shared__ int counters[2];                     // |in|, |undecided|
+  __shared__ int counters[kRescore ? kBinRounds : 1][2];   // of each round: |in|, |undecided|
 
   const int n_app = ap.app.knew ? a.batch * append_wgs<T>(a.H, ap.D) : 0;
   if ((int)blockIdx.x < n_app) {                  // uniform: an append workgroup
@@ -1656,14 +1676,21 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(D > 128 ? 2 :
       for (int t = 0; t < kQRounds; t++) qv[t] = qsrc[min(tid + T * t, nq - 1)];
     }
     for (int x = tid; x < 2 * kBins / 4; x += T) reinterpret_cast<int4*>(&hist[0][0])[x] = make_int4(0, 0, 0, 0);
-    if (tid < 2) counters[tid] = 0;
+    if (tid < 2 * (kRescore ? kBinRounds : 1)) (&counters[0][0])[tid] = 0;
+    uint32_t um = 0;                                 // bit x: the page of slot x is undecided
+    SlotWords<T, K> sw;                              // this wave's chosen pages
     float lo_min = INFINITY, hi_max = -INFINITY;
 #pragma unroll
     for (int x = 0; x < K; x++) {
-      if (x * T < P && is_cand(x * T + tid)) {
-        lo_min = fminf(lo_min, lf[x]);
-        if constexpr (kRescore) hi_max = fmaxf(hi_max, uf[x]);
-        else hi_max = fmaxf(hi_max, lf[x]);
+      if (x * T < P) {
+        const bool cand = is_cand(x * T + tid);
+        if (cand) {
+          um |= 1u << x;
+          lo_min = fminf(lo_min, lf[x]);
+          if constexpr (kRescore) hi_max = fmaxf(hi_max, uf[x]);
+          else hi_max = fmaxf(hi_max, lf[x]);
+        }
+        sw.put(x, __ballot(x * T + tid < P && !cand));   // forced pages are chosen
       }
     }
     if constexpr (kMeanRescore) {
@@ -1688,34 +1715,22 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(D > 128 ? 2 :
         }
       }
     }
-    lo_min = wave_min_f32(lo_min);
-    hi_max = wave_max_f32(hi_max);
-    if (lane == 0) {
-      mm[0][w] = __float_as_uint(lo_min);
-      mm[1][w] = __float_as_uint(hi_max);
-    }
-    __syncthreads();
-#pragma unroll
-    for (int x = 0; x < S::W; x++) {
-      lo_min = fminf(lo_min, __uint_as_float(mm[0][x]));
-      hi_max = fmaxf(hi_max, __uint_as_float(mm[1][x]));
-    }
-    const float span = hi_max - lo_min;
-    const float scale = (span > 0.f && span < INFINITY) ? (float)kBins / span : 0.f;
-    // NaN bounds (and any with scale 0) fall into bin 0
-    auto bin_of = [&](float x) { return (int)fminf(fmaxf((x - lo_min) * scale, 0.f), (float)(kBins - 1)); };
-    int bl[K], bu[kRescore ? K : 1];
-#pragma unroll
-    for (int x = 0; x < K; x++) {
-      if (x * T < P) {
-        bl[x] = bin_of(lf[x]);
-        if constexpr (kRescore) bu[x] = bin_of(uf[x]);
-        if (is_cand(x * T + tid)) {
-          atomicAdd(&hist[0][bl[x]], 1);
-          if constexpr (kRescore) atomicAdd(&hist[1][bu[x]], 1);
-        }
+    // the range over the workgroup, behind a barrier
+    auto block_range = [&]() {
+      lo_min = wave_min_f32(lo_min);
+      hi_max = wave_max_f32(hi_max);
+      if (lane == 0) {
+        mm[0][w] = __float_as_uint(lo_min);
+        mm[1][w] = __float_as_uint(hi_max);
       }
-    }
+      __syncthreads();
+#pragma unroll
+      for (int x = 0; x < S::W; x++) {
+        lo_min = fminf(lo_min, __uint_as_float(mm[0][x]));
+        hi_max = fmaxf(hi_max, __uint_as_float(mm[1][x]));
+      }
+    };
+    block_range();
     if constexpr (kMeanRescore) {
       // group-mean query: fp64 sums in head order, then finish_qbar's division (as one pass)
       const uint16_t* qh = reinterpret_cast<const uint16_t*>(qraw);
@@ -1725,92 +1740,118 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(D > 128 ? 2 :
         qbar[c] = c < a.qdims ? finish_qbar_one(acc, g) : 0.0;
       }
     }
-    __syncthreads();
-    // at least K_free + 1 candidates exist: P > K_total
-    if (w == 0) wave_pick_bin(hist[0], s.Kfree, pick[0]);
-    if (w == S::W - 1) wave_pick_bin(hist[kRescore ? 1 : 0], s.Kfree + 1, pick[1]);
-    __syncthreads();
-    const int t_lo = pick[0][0];                     // bin of the K-th largest lower bound
-    const int t_hi = pick[1][0];                     // bin of the (K+1)-th largest upper bound
-    uint32_t um = 0;                                 // bit x: the page of slot x is undecided
-    uint64_t mu[K];                                  // this wave's undecided pages of slot x
-    int n_in = 0, n_mine = 0;                        // this wave's counts
-    SlotWords<T, K> sw;
-#pragma unroll
-    for (int x = 0; x < K; x++) {
-      mu[x] = 0;
-      if (x * T < P) {
-        const int j = x * T + tid;
-        const bool cand = is_cand(j);
-        bool u = bl[x] >= t_lo;
-        if constexpr (kRescore) u = bu[x] >= t_lo;
-        const bool in = cand && bl[x] > t_hi;
-        u = u && cand && !in;
-        um |= u ? 1u << x : 0u;
-        mu[x] = __ballot(u);
-        n_in += __popcll(__ballot(in));
-        n_mine += __popcll(mu[x]);
-        sw.put(x, __ballot(in || (j < P && !cand)));   // forced pages are chosen
-      }
-    }
-    sw.store(words, w, P);
-    int at = 0;
-    if (lane == 0) {
-      if (n_in) atomicAdd(&counters[0], n_in);
-      if (n_mine) at = atomicAdd(&counters[1], n_mine);
-    }
-    if (n_mine) {                                    // uniform over the wave
-      at = __builtin_amdgcn_readfirstlane(at);
+    int need = s.Kfree, n_und;
+#pragma clang loop unroll(disable)
+    for (int round = 0;; round++) {
+      int Pr = P;                                    // the slots' tests are made in the round: kept around
+      asm volatile("" : "+s"(Pr));                   // the loop they spill
+      const float origin = lo_min, scale = bin_scale(lo_min, hi_max);
+      // NaN bounds (and any with scale 0) fall into bin 0
+      auto bin_of = [&](float x) { return (int)fminf(fmaxf((x - origin) * scale, 0.f), (float)(kBins - 1)); };
+      int bl[K], bu[kRescore ? K : 1];
 #pragma unroll
       for (int x = 0; x < K; x++) {
-        if (mu[x]) {
-          const int pos = at + __builtin_amdgcn_mbcnt_hi((uint32_t)(mu[x] >> 32),
-                                                         __builtin_amdgcn_mbcnt_lo((uint32_t)mu[x], 0u));
+        if (x * T < Pr) {
+          bl[x] = bin_of(lf[x]);
+          if constexpr (kRescore) bu[x] = bin_of(uf[x]);
           if ((um >> x) & 1u) {
-            if constexpr (kRescore) {
-              if (pos < kMaxUndecided) und[pos] = x * T + tid;
-            } else if (pos < kWave) {
-              und[pos] = x * T + tid;
-              und_key[pos] = float_key(lf[x]);
-            }
+            atomicAdd(&hist[0][bl[x]], 1);
+            if constexpr (kRescore) atomicAdd(&hist[1][bu[x]], 1);
           }
-          at += __popcll(mu[x]);
         }
       }
-    }
-    __syncthreads();
-    int need = s.Kfree - counters[0];
-    const int n_und = counters[1];
-    if (need > 0 && need >= n_und) {                 // every undecided page is chosen
+      __syncthreads();
+      // at least need + 1 undecided pages exist (at first P > K_total)
+      if (w == 0) wave_pick_bin(hist[0], need, pick[0]);
+      if (w == S::W - 1) wave_pick_bin(hist[kRescore ? 1 : 0], need + 1, pick[1]);
+      __syncthreads();
+      const int t_lo = pick[0][0];                   // bin of the need-th largest lower bound
+      const int t_hi = pick[1][0];                   // bin of the (need + 1)-th largest upper bound
+      uint64_t mu[K];                                // this wave's undecided pages of slot x
+      int n_in = 0, n_mine = 0;                      // this wave's counts
 #pragma unroll
       for (int x = 0; x < K; x++) {
-        if (mu[x] && lane == 0) {
-          uint2& v = words[x * S::W + w];
-          v = make_uint2(v.x | (uint32_t)mu[x], v.y | (uint32_t)(mu[x] >> 32));
+        mu[x] = 0;
+        if (x * T < Pr) {
+          const bool was = (um >> x) & 1u;
+          bool u = bl[x] >= t_lo;
+          if constexpr (kRescore) u = bu[x] >= t_lo;
+          const bool in = was && bl[x] > t_hi;
+          u = u && was && !in;
+          um = u ? um : um & ~(1u << x);
+          mu[x] = __ballot(u);
+          const uint64_t mi = __ballot(in);
+          n_in += __popcll(mi);
+          n_mine += __popcll(mu[x]);
+          sw.add(x, mi);
         }
       }
-    } else if (need > 0) {
-      const bool rescore_all = kRescore && n_und > kMaxUndecided;
-      if (rescore_all) {
-        // pathological overlap of the bounds: re-score every candidate instead
-        need = s.Kfree;
-        um = 0;
-        SlotWords<T, K> fw;
+      sw.store(words, w, Pr);
+      // the undecided list (in any order), and the counts
+      int at = 0;
+      if (lane == 0) {
+        if (n_in) atomicAdd(&counters[round][0], n_in);
+        if (n_mine) at = atomicAdd(&counters[round][1], n_mine);
+      }
+      if (n_mine) {                                  // uniform over the wave
+        at = __builtin_amdgcn_readfirstlane(at);
 #pragma unroll
         for (int x = 0; x < K; x++) {
-          if (x * T < P) {
-            const int j = x * T + tid;
-            const bool cand = is_cand(j);
-            um |= cand ? 1u << x : 0u;
-            fw.put(x, __ballot(j < P && !cand));
+          if (mu[x]) {
+            const int pos = at + __builtin_amdgcn_mbcnt_hi((uint32_t)(mu[x] >> 32),
+                                                           __builtin_amdgcn_mbcnt_lo((uint32_t)mu[x], 0u));
+            if ((um >> x) & 1u) {
+              if constexpr (kRescore) {
+                if (pos < kMaxUndecided) und[pos] = x * T + tid;
+              } else if (pos < kWave) {
+                und[pos] = x * T + tid;
+                und_key[pos] = float_key(lf[x]);
+              }
+            }
+            at += __popcll(mu[x]);
           }
         }
-        fw.store(words, w, P);
       }
-      // exact scores of the undecided pages: rows of 16 lanes, two pages per row at a time
+      __syncthreads();
+      need -= counters[round][0];
+      n_und = counters[round][1];
+      if constexpr (!kRescore) break;
+      // Both thresholds in one bin or in neighbours: the bins, not the bounds, leave the pages
+      // undecided.
+      if (round == kBinRounds - 1 || t_hi - t_lo > 1 || need == 0 || need >= n_und ||
+          n_und <= min(kWave, T / 8))                // uniform
+        break;
+      lo_min = INFINITY;
+      hi_max = -INFINITY;
+#pragma unroll
+      for (int x = 0; x < K; x++) {
+        if ((um >> x) & 1u) {
+          if (bin_of(lf[x]) == t_lo && fabsf(lf[x]) < INFINITY) {
+            lo_min = fminf(lo_min, lf[x]);
+            hi_max = fmaxf(hi_max, lf[x]);
+          }
+          if (bin_of(uf[x]) == t_hi && fabsf(uf[x]) < INFINITY) {
+            lo_min = fminf(lo_min, uf[x]);
+            hi_max = fmaxf(hi_max, uf[x]);
+          }
+        }
+      }
+      for (int x = tid; x < 2 * kBins / 4; x += T) reinterpret_cast<int4*>(&hist[0][0])[x] = make_int4(0, 0, 0, 0);
+      block_range();
+      if (!(hi_max > lo_min)) break;                 // one value, or none finite: uniform
+    }
+    if (need > 0 && need >= n_und) {                 // every undecided page is chosen
+#pragma unroll
+      for (int x = 0; x < K; x++)
+        if (x * T < P) sw.add(x, __ballot((um >> x) & 1u));
+      sw.store(words, w, P);
+    } else if (need > 0) {
+      // exact scores of the undecided pages (more than the list holds: of every page): rows of 16
+      // lanes, kAt pages per row at a time, the next ones and the page ids after those on their way
       if constexpr (kRescore) {
-        constexpr int kRowsT = T / 16;
-        const int n_score = rescore_all ? P : n_und;
+        constexpr int kRowsT = T / 16, kAt = T > 512 && kMeanRescore ? 4 : 2;
+        const bool listed = n_und <= kMaxUndecided;
+        const int n_score = listed ? n_und : P;
         const int row16 = tid >> 4, u = tid & 15;
         double qb[kMeanRescore ? E : 1];
         if constexpr (kMeanRescore) {
@@ -1819,43 +1860,76 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(D > 128 ? 2 :
 #pragma unroll
             for (int e = 0; e < 4; e++) qb[4 * c + e] = qbar[M::channel(u, c, e)];
         }
-        for (int x0 = row16; x0 < n_score; x0 += 2 * kRowsT) {
-          const int x1 = x0 + kRowsT;
-          const bool has1 = x1 < n_score;
-          const int j0 = rescore_all ? x0 : und[x0];
-          const int j1 = has1 ? (rescore_all ? x1 : und[x1]) : j0;
-          const int64_t p0 = block_row(a.indices + s.base, j0, a.r, a.num_phys);
-          const int64_t p1 = block_row(a.indices + s.base, j1, a.r, a.num_phys);
-          float s0, s1;
-          if constexpr (kMeanRescore) {
-            uint32_t w0[RowWords<DD, false>::W], w1[RowWords<DD, false>::W];
-            load_row_words<DD, false>(a.mean + (p0 * a.H + s.h) * D, u, w0);
-            load_row_words<DD, false>(a.mean + (p1 * a.H + s.h) * D, u, w1);
-            s0 = exact_row_score<DD, false>(qb, w0);
-            s1 = exact_row_score<DD, false>(qb, w1);
-          } else {
-            constexpr int WW = RowWords<DD, true>::W;
-            uint32_t a0[WW], a1[WW], b0[needs_min(RK) ? WW : 1], b1[needs_min(RK) ? WW : 1];
-            load_row_words<DD, true>(a.maxs + (p0 * a.H + s.h) * D, u, a0);
-            load_row_words<DD, true>(a.maxs + (p1 * a.H + s.h) * D, u, a1);
-            if constexpr (needs_min(RK)) {
-              load_row_words<DD, true>(a.mins + (p0 * a.H + s.h) * D, u, b0);
-              load_row_words<DD, true>(a.mins + (p1 * a.H + s.h) * D, u, b1);
-              s0 = (float)env_exact<RK, DD>(qs, 0, g, u, a0, b0);
-              s1 = (float)env_exact<RK, DD>(qs, 0, g, u, a1, b1);
-            } else {
-              s0 = (float)env_exact<RK, DD>(qs, 0, g, u, a0, a0);
-              s1 = (float)env_exact<RK, DD>(qs, 0, g, u, a1, a1);
+        constexpr int WM = RowWords<DD, !kMeanRescore>::W;
+        struct Rows {
+          uint32_t a[kAt][WM];                         // Mean / Max rows
+          uint32_t b[kAt][needs_min(RK) ? WM : 1];     // Min rows
+        };
+        // Batch b: pages row16 + (b kAt + v) kRowsT, v < N; past the last page, that page again.
+        const int rsh = 31 - __clz(a.r);                           // blocks per page: 1, 2 or 4
+        auto page_at = [&](int x) {
+          const int y = min(x, n_score - 1), j = und[min(y, kMaxUndecided - 1)];
+          return listed ? j : y;
+        };
+        struct Ids {
+          int j[kAt], page[kAt];
+        };
+        auto load_ids = [&](int b, Ids& id, auto n) {
+#pragma unroll
+          for (int v = 0; v < decltype(n)::value; v++) {
+            id.j[v] = page_at((b * kAt + v) * kRowsT + row16);
+            id.page[v] = a.indices[s.base + (id.j[v] >> rsh)];
+          }
+        };
+        auto load_rows = [&](const Ids& id, Rows& pr, auto n) {
+#pragma unroll
+          for (int v = 0; v < decltype(n)::value; v++) {
+            const int64_t block = (clamp_page(id.page[v], a.num_phys) << rsh) + (id.j[v] & (a.r - 1));
+            const int64_t at = (block * a.H + s.h) * D;
+            if constexpr (kMeanRescore) load_row_words<DD, false>(a.mean + at, u, pr.a[v]);
+            else load_row_words<DD, true>(a.maxs + at, u, pr.a[v]);
+            if constexpr (needs_min(RK)) load_row_words<DD, true>(a.mins + at, u, pr.b[v]);
+          }
+        };
+        auto score = [&](int b, const Rows& pr, auto n) {
+#pragma unroll
+          for (int v = 0; v < decltype(n)::value; v++) {
+            float sc;
+            if constexpr (kMeanRescore) sc = exact_row_score<DD, false>(qb, pr.a[v]);
+            else if constexpr (needs_min(RK)) sc = (float)env_exact<RK, DD>(qs, 0, g, u, pr.a[v], pr.b[v]);
+            else sc = (float)env_exact<RK, DD>(qs, 0, g, u, pr.a[v], pr.a[v]);
+            const int x = (b * kAt + v) * kRowsT + row16;
+            if (u == 0 && x < n_score) {
+              if (n_und <= kWave) und_key[x] = float_key(sc);
+              else exact_keys[page_at(x)] = float_key(sc);         // decided pages' keys are never read
             }
           }
-          if (u == 0) {
-            if (n_und <= kWave) {
-              und_key[x0] = float_key(s0);
-              if (has1) und_key[x1] = float_key(s1);
-            } else {
-              exact_keys[j0] = float_key(s0);       // forced pages' keys are never read
-              if (has1) exact_keys[j1] = float_key(s1);
-            }
+        };
+        Ids id;
+        Rows ra, rb;
+        const int batches = (n_score + kAt * kRowsT - 1) / (kAt * kRowsT);   // uniform
+        if (n_score <= 2 * kRowsT) {                               // uniform: all at once
+          auto once = [&](auto n) {
+            load_ids(0, id, n);
+            load_rows(id, ra, n);
+            score(0, ra, n);
+          };
+          if (n_score <= kRowsT) once(std::integral_constant<int, 1>{});
+          else once(std::integral_constant<int, 2>{});
+        } else {
+          using All = std::integral_constant<int, kAt>;
+          load_ids(0, id, All{});
+          load_rows(id, ra, All{});
+          load_ids(1, id, All{});
+          for (int b = 0;; b += 2) {                               // uniform
+            if (b + 1 < batches) load_rows(id, rb, All{});
+            if (b + 2 < batches) load_ids(b + 2, id, All{});
+            score(b, ra, All{});
+            if (b + 1 >= batches) break;
+            if (b + 2 < batches) load_rows(id, ra, All{});
+            if (b + 3 < batches) load_ids(b + 3, id, All{});
+            score(b + 1, rb, All{});
+            if (b + 2 >= batches) break;
           }
         }
         __syncthreads();

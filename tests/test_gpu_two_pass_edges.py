@@ -82,3 +82,37 @@ def test_first_pass_out_of_range(kind, D, P):
     scores = pb.check(kind)
     assert torch.isfinite(scores).all()
     assert (scores[:, :, top] == D / 2 * mag * 2.0 ** 113).all()
+
+
+SHAPES = [(vx.MEAN_DOT, 128, 4097, 2, 2), (vx.MEAN_DOT, 128, 8193, 1, 2), (vx.MEAN_DOT, 128, 16384, 1, 1),
+          (vx.QUEST, 128, 4097, 2, 2), (vx.QUEST, 128, 8193, 1, 2), (vx.QUEST, 64, 16384, 1, 1),
+          (vx.QUEST_RECTIFIED, 128, 8192, 1, 2), (vx.QUEST_CONSENSUS, 128, 16384, 1, 1),
+          (vx.ENVELOPE_LOWER, 128, 4100, 2, 1), (vx.MEAN_DOT, 64, 1500, 40, 16), (vx.QUEST, 64, 2500, 40, 16),
+          (vx.QUEST, 128, 600, 3, 2), (vx.MEAN_DOT, 576, 1025, 2, 1), (vx.MEAN_DOT, 576, 2049, 2, 1),
+          (vx.MEAN_DOT, 576, 4097, 2, 1), (vx.MEAN_DOT, 576, 8193, 1, 1), (vx.MEAN_DOT, 576, 16384, 1, 1),
+          (vx.MEAN_DOT, 576, 2100, 520, 1)]
+
+
+@pytest.mark.parametrize("rows", ["spread", "far", "farther", "near", "equal", "infinite"])
+@pytest.mark.parametrize("kind,D,P,B,H", SHAPES)
+def test_two_pass_shapes(kind, D, P, B, H, rows):
+    """Ordinary rows; one block scaled by 300; one by 1e6 and one by 1e3, of both signs, so that the bins
+    are refined more than once; blocks that differ by a hundredth (most are undecided by the block mean's
+    bounds) or not at all; an infinite channel, whose score is infinite or NaN."""
+    pb = Problem(D, P, B, H, 16 if D == 576 else 4, 3 * D + P + B)
+    if rows in ("far", "farther"):
+        for i in range(B):
+            for block, f in [(7, 300.0)] if rows == "far" else [(7, 1e6), (P // 3 - 4, -1e3)]:
+                r = pb.rows(i, [block])
+                pb.mean[r] *= f
+                a, b = pb.max[r] * f, pb.min[r] * f
+                pb.max[r], pb.min[r] = torch.maximum(a, b), torch.minimum(a, b)
+    elif rows in ("near", "equal"):
+        for s in (pb.mean, pb.max, pb.min):
+            s.mul_(0.01 if rows == "near" else 0.0).add_(s[:1] * 100 if rows == "near" else 0.375)
+    elif rows == "infinite":
+        for i in range(B):
+            for block, x in [(7, float("inf")), (9, float("-inf")), (P // 3 - 4, float("inf"))]:
+                for s in (pb.mean, pb.max, pb.min):
+                    s[pb.rows(i, [block]), :, 3] = x
+    pb.check(kind)
