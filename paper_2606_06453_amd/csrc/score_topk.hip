@@ -11,12 +11,14 @@
 //                bounds with re-scoring of the pages they leave undecided, by one histogram of
 //                equal-width bins; topk_wave_kernel does it in one wave for short requests.
 // topk_radix_kernel  The options' radix selection on the same page slots.
-// topk_long_kernel  (requests past the slots of both) One workgroup per (request, KV head).  It runs an exact radix select over
+// topk_long_kernel  (request bounds past the slots of both) One workgroup per (request, KV head).
+//                Rows that fit page slots take the radix selection above; longer ones run the same
+//                exact radix select over
 //                an order-preserving uint32 key of the fp32 score.  Passes start at the
 //                highest bit where the candidates' smallest and largest keys differ and take
 //                up to 8 bits each.  Each pass builds a double-buffered LDS histogram, and
-//                one wave scans its bins.  Each pass re-reads the scores; all score loads are
-//                issued in one round trip.  That finds the K_free-th best candidate.
+//                one wave scans its bins.  Each pass re-reads the scores from memory.  That finds
+//                the K_free-th best candidate.
 //                Ties at the threshold go to the lowest page index.  Each thread owns a
 //                contiguous page range: one block scan ranks the tied pages and a second
 //                compacts the forced and chosen pages in ascending order.
@@ -1121,203 +1123,6 @@ __device__ __forceinline__ void block_fminmax(float& mn, float& mx, float (*wave
   }
 }
 
-// items == nullptr: the request's page count from seq_lens and the page list; else items[i]
-// (capped at the row stride).
-//
-// The radix selection of rows past kTwoPassMaxPages.  Thread t owns the contiguous pages
-// [t*R, t*R + R), R = ceil(P / kThreads), and every pass recomputes their keys from the scores
-// (L2-resident after the first read).
-__global__ __launch_bounds__(kThreads) void topk_long_kernel(
-    const float* __restrict__ scores, int H, int ps, int r, int max_pages, int stride, int batch,
-    const int32_t* __restrict__ indptr, const int32_t* __restrict__ seq_lens, const int32_t* __restrict__ items,
-    const int32_t* __restrict__ budget, int n_sink, int n_local, int max_sel, const TopkOptions opt,
-    int32_t* __restrict__ sel_pages, int32_t* __restrict__ sel_count) {
-  __shared__ int hist[2][256];
-  __shared__ int wave_tot[kThreads / kWave];
-  __shared__ uint32_t wave_mm[2][kThreads / kWave];
-  __shared__ float wave_fm[2][kThreads / kWave];
-  __shared__ int pick[2][3];           // digit, count above the digit's bin, bin count
-
-  const int tid = threadIdx.x, lane = lane_id(), w = tid >> 6;
-  const int i = blockIdx.x / H, h = blockIdx.x % H;
-  const int P = items ? min(max(items[i], 0), stride)
-                      : num_pages(seq_lens[i], ps, (indptr[i + 1] - indptr[i]) * r, max_pages);
-  int Ktot = budget[i];
-  Ktot = Ktot < max_sel ? Ktot : max_sel;
-  Ktot = Ktot < 0 ? 0 : Ktot;
-  const float* s = scores + ((int64_t)h * batch + i) * stride;
-  int32_t* out = sel_pages + ((int64_t)i * H + h) * max_sel;
-
-  const bool all = Ktot >= P;
-  const int nS = min(n_sink, P), nL = min(n_local, P);
-  const int nF = all ? P : nS + nL - max(0, nS - (P - nL));
-  const int Kfree = all ? 0 : max(0, Ktot - nF);
-  const int R = (P + kThreads - 1) / kThreads;
-  const int j_lo = min(P, tid * R), n_mine = min(P, j_lo + R) - j_lo;
-
-  double rmin = 0.0, rscale = 0.0;                       // remap 1: min and scale of the affine map
-  auto make_key = [&](float x) -> uint32_t {
-    if (opt.remap == 0) return float_key(x);
-    if (x != x) return 0u;
-    // in [0, 2^32 - 1] for candidates; forced pages (never ranked) may fall outside: clamp
-    return (uint32_t)fmin(fmax(floor(((double)x - rmin) * rscale), 0.0), 4294967295.0);
-  };
-  // f(j, key) for every candidate of this thread
-  auto each_candidate = [&](auto&& f) {
-    for (int j = j_lo; j < j_lo + n_mine; j++)
-      if (!is_forced(j, P, nS, nL)) f(j, make_key(s[j]));
-  };
-  // Radix select over the candidates' keys.  Threshold prefix: a candidate is chosen when
-  // (key & pmask) > prefix, or when it equals the prefix and its rank among equals (by page
-  // index; after an early stop by (h8 desc, page)) is below `remaining`.
-  uint32_t prefix = 0, pmask = 0;
-  int remaining = Kfree;
-  int hthr = -1;                                         // stopped early: hash threshold h8
-  uint32_t hz = 0;                                       // hash salt z of this (request, head)
-  // Wave 0 finds the bin of histogram hb holding the remaining-th largest digit (lane l owns
-  // bins 255-4l .. 252-4l, descending): pick[hb] = {bin, count above it, bin count}.
-  auto pick_bin = [&](int hb) {
-    if (w == 0) {
-      int c[4], tot = 0;
-#pragma unroll
-      for (int e = 0; e < 4; e++) {
-        c[e] = hist[hb][255 - 4 * lane - e];
-        tot += c[e];
-      }
-      int above = wave_incl_sum(tot) - tot;
-#pragma unroll
-      for (int e = 0; e < 4; e++) {
-        if (above < remaining && above + c[e] >= remaining) {
-          pick[hb][0] = 255 - 4 * lane - e;
-          pick[hb][1] = above;
-          pick[hb][2] = c[e];
-        }
-        above += c[e];
-      }
-    }
-    __syncthreads();
-  };
-  if (Kfree > 0) {
-    if (opt.remap != 0) {
-      // the candidates' score range (NaN excluded) fixes the affine map
-      float fmn = INFINITY, fmx = -INFINITY;
-      for (int j = j_lo; j < j_lo + n_mine; j++) {
-        const float x = s[j];
-        if (!is_forced(j, P, nS, nL) && x == x) {
-          fmn = fminf(fmn, x);
-          fmx = fmaxf(fmx, x);
-        }
-      }
-      block_fminmax(fmn, fmx, wave_fm);
-      rmin = (double)fmn;
-      rscale = fmx > fmn ? 4294967295.0 / ((double)fmx - (double)fmn) : 0.0;
-    }
-    // bits above the highest bit where the smallest and largest candidate key differ are
-    // common to every candidate and need no pass
-    uint32_t kmin = 0xffffffffu, kmax = 0u;
-    each_candidate([&](int, uint32_t key) {
-      kmin = min(kmin, key);
-      kmax = max(kmax, key);
-    });
-    kmin = wave_min_u32(kmin);
-    kmax = wave_max_u32(kmax);
-    if (lane == 0) {
-      wave_mm[0][w] = kmin;
-      wave_mm[1][w] = kmax;
-    }
-    hist[0][tid] = 0;
-    __syncthreads();
-#pragma unroll
-    for (int x = 0; x < kThreads / kWave; x++) {
-      kmin = min(kmin, wave_mm[0][x]);
-      kmax = max(kmax, wave_mm[1][x]);
-    }
-    const uint32_t diff = kmin ^ kmax;
-    int top = diff ? 31 - __clz((int)diff) : -1;           // highest differing bit
-    pmask = top >= 31 ? 0u : ~((2u << top) - 1u);           // common high bits
-    if (top < 0) pmask = 0xffffffffu;                        // all candidate keys equal
-    prefix = kmin & pmask;
-
-    int hb = 0, certain = 0;
-    while (top >= 0) {
-      const int shift = top >= 7 ? top - 7 : 0;
-      const uint32_t dmask = (1u << (top - shift + 1)) - 1u;   // 1..8 bits
-      hist[hb ^ 1][tid] = 0;                                   // next pass's histogram
-      each_candidate([&](int, uint32_t key) {
-        if ((key & pmask) == prefix) atomicAdd(&hist[hb][(key >> shift) & dmask], 1);
-      });
-      __syncthreads();
-      pick_bin(hb);
-      remaining -= pick[hb][1];
-      certain += pick[hb][1];
-      prefix |= (uint32_t)pick[hb][0] << shift;
-      pmask |= dmask << shift;
-      const bool done = pick[hb][2] == remaining;   // every key with this prefix is chosen
-      top = shift - 1;
-      hb ^= 1;
-      if (done) break;
-      if (top >= 0 && (int64_t)certain * 65536 >= (int64_t)(65536 - opt.tau_q) * Kfree) {
-        // early termination: one pass over the threshold bin's hashes (histogram hb was
-        // cleared during the last pass) orders the rest at random
-        hz = lowbias32(opt.seed ^ lowbias32((uint32_t)(i * H + h)));
-        each_candidate([&](int j, uint32_t key) {
-          if ((key & pmask) == prefix) atomicAdd(&hist[hb][lowbias32(hz ^ (uint32_t)j) >> 24], 1);
-        });
-        __syncthreads();
-        pick_bin(hb);
-        remaining -= pick[hb][1];
-        hthr = pick[hb][0];
-        break;
-      }
-    }
-  }
-
-  // Compaction: one scan gives each tied candidate its rank by page index, a second gives each
-  // chosen page its slot.
-  // After an early stop a bin member ranks above the tie class by its hash, else ties.
-  auto hash_cmp = [&](int j) -> int {
-    if (hthr < 0) return 0;
-    const int hv = (int)(lowbias32(hz ^ (uint32_t)j) >> 24);
-    return (hv > hthr) - (hv < hthr);
-  };
-  int n_eq = 0;
-  if (Kfree > 0) {
-    each_candidate([&](int j, uint32_t key) { n_eq += (key & pmask) == prefix && hash_cmp(j) == 0; });
-  }
-  int tot_eq;
-  const int eq_rank = block_incl_scan(n_eq, wave_tot, &tot_eq) - n_eq;
-  // the tie class's chosen members are its `remaining` lowest page indices
-  auto chosen_at = [&](int j, uint32_t key, int& r) -> bool {
-    if (all || is_forced(j, P, nS, nL)) return true;
-    if (Kfree <= 0) return false;
-    const uint32_t mk = key & pmask;
-    if (mk != prefix) return mk > prefix;
-    const int hc = hash_cmp(j);
-    if (hc != 0) return hc > 0;
-    const bool in = r < remaining;
-    r++;
-    return in;
-  };
-  int n_chosen = 0;
-  {
-    int r = eq_rank;
-    for (int j = j_lo; j < j_lo + n_mine; j++) n_chosen += chosen_at(j, Kfree > 0 ? make_key(s[j]) : 0u, r);
-  }
-  int tot_sel;
-  int pos = block_incl_scan(n_chosen, wave_tot, &tot_sel) - n_chosen;
-  {
-    int r = eq_rank;
-    for (int j = j_lo; j < j_lo + n_mine; j++) {
-      if (chosen_at(j, Kfree > 0 ? make_key(s[j]) : 0u, r)) {
-        if (pos < max_sel) out[pos] = j;
-        pos++;
-      }
-    }
-  }
-  for (int m = tot_sel + tid; m < max_sel; m += kThreads) out[m] = -1;
-  if (h == 0 && tid == 0) sel_count[i] = min(tot_sel, max_sel);
-}
-
 struct RadixState {
   uint32_t prefix, pmask;   // resolved high bits of the k-th largest key
   int top;                  // highest unresolved bit, -1 when done
@@ -2056,7 +1861,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(D > 128 ? 2 :
 // of up to 3000 scores 19.3 -> 8.8.
 // ------------------------------------------------------------------------------------
 template <int T, int K>
-__global__ __launch_bounds__(T) void topk_radix_kernel(const SelArgs a, const TopkOptions opt) {
+__device__ __forceinline__ void radix_select_slots(const SelArgs& a, const SelRow& s, const TopkOptions& opt) {
   using S = SelShape<T, K>;
   __shared__ __align__(16) int hist[3][256];
   __shared__ uint2 words[S::kWords];              // chosen pages
@@ -2064,7 +1869,6 @@ __global__ __launch_bounds__(T) void topk_radix_kernel(const SelArgs a, const To
   __shared__ uint32_t mm[2][S::W];
   const int tid = (int)threadIdx.x, lane = lane_id();
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const SelRow s = sel_row(a, (int)blockIdx.x, S::M);
   const int P = s.P;
   auto is_cand = [&](int j) { return !s.all && j >= s.nS && j < P - s.nL; };
   SlotWords<T, K> sw;
@@ -2240,6 +2044,205 @@ __global__ __launch_bounds__(T) void topk_radix_kernel(const SelArgs a, const To
   sw.store(words, w, P);
   __syncthreads();
   write_selection<T, K>(a, s, words, w);
+}
+
+template <int T, int K>
+__global__ __launch_bounds__(T) void topk_radix_kernel(const SelArgs a, const TopkOptions opt) {
+  radix_select_slots<T, K>(a, sel_row(a, (int)blockIdx.x, T * K), opt);
+}
+
+// ------------------------------------------------------------------------------------
+// The radix selection past the page slots.  Thread t owns the contiguous pages [t*R, t*R + R),
+// R = ceil(P / kThreads), and every pass recomputes their keys from the scores (L2-resident after
+// the first read).
+// ------------------------------------------------------------------------------------
+__device__ __forceinline__ void radix_select_long(const SelArgs& a, const SelRow& row, const TopkOptions& opt) {
+  __shared__ int hist[2][256];
+  __shared__ int wave_tot[kThreads / kWave];
+  __shared__ uint32_t wave_mm[2][kThreads / kWave];
+  __shared__ float wave_fm[2][kThreads / kWave];
+  __shared__ int pick[2][3];           // digit, count above the digit's bin, bin count
+
+  const int tid = threadIdx.x, lane = lane_id(), w = tid >> 6;
+  const int i = row.i, h = row.h, P = row.P, nS = row.nS, nL = row.nL, Kfree = row.Kfree, max_sel = a.max_sel;
+  const bool all = row.all;
+  const float* s = a.lower + ((int64_t)h * a.batch + i) * a.stride;
+  int32_t* out = row.out;
+  const int R = (P + kThreads - 1) / kThreads;
+  const int j_lo = min(P, tid * R), n_mine = min(P, j_lo + R) - j_lo;
+
+  double rmin = 0.0, rscale = 0.0;                       // remap 1: min and scale of the affine map
+  auto make_key = [&](float x) -> uint32_t {
+    if (opt.remap == 0) return float_key(x);
+    if (x != x) return 0u;
+    // in [0, 2^32 - 1] for candidates; forced pages (never ranked) may fall outside: clamp
+    return (uint32_t)fmin(fmax(floor(((double)x - rmin) * rscale), 0.0), 4294967295.0);
+  };
+  // f(j, key) for every candidate of this thread
+  auto each_candidate = [&](auto&& f) {
+    for (int j = j_lo; j < j_lo + n_mine; j++)
+      if (!is_forced(j, P, nS, nL)) f(j, make_key(s[j]));
+  };
+  // Radix select over the candidates' keys.  Threshold prefix: a candidate is chosen when
+  // (key & pmask) > prefix, or when it equals the prefix and its rank among equals (by page
+  // index; after an early stop by (h8 desc, page)) is below `remaining`.
+  uint32_t prefix = 0, pmask = 0;
+  int remaining = Kfree;
+  int hthr = -1;                                         // stopped early: hash threshold h8
+  uint32_t hz = 0;                                       // hash salt z of this (request, head)
+  // Wave 0 finds the bin of histogram hb holding the remaining-th largest digit (lane l owns
+  // bins 255-4l .. 252-4l, descending): pick[hb] = {bin, count above it, bin count}.
+  auto pick_bin = [&](int hb) {
+    if (w == 0) {
+      int c[4], tot = 0;
+#pragma unroll
+      for (int e = 0; e < 4; e++) {
+        c[e] = hist[hb][255 - 4 * lane - e];
+        tot += c[e];
+      }
+      int above = wave_incl_sum(tot) - tot;
+#pragma unroll
+      for (int e = 0; e < 4; e++) {
+        if (above < remaining && above + c[e] >= remaining) {
+          pick[hb][0] = 255 - 4 * lane - e;
+          pick[hb][1] = above;
+          pick[hb][2] = c[e];
+        }
+        above += c[e];
+      }
+    }
+    __syncthreads();
+  };
+  if (Kfree > 0) {
+    if (opt.remap != 0) {
+      // the candidates' score range (NaN excluded) fixes the affine map
+      float fmn = INFINITY, fmx = -INFINITY;
+      for (int j = j_lo; j < j_lo + n_mine; j++) {
+        const float x = s[j];
+        if (!is_forced(j, P, nS, nL) && x == x) {
+          fmn = fminf(fmn, x);
+          fmx = fmaxf(fmx, x);
+        }
+      }
+      block_fminmax(fmn, fmx, wave_fm);
+      rmin = (double)fmn;
+      rscale = fmx > fmn ? 4294967295.0 / ((double)fmx - (double)fmn) : 0.0;
+    }
+    // bits above the highest bit where the smallest and largest candidate key differ are
+    // common to every candidate and need no pass
+    uint32_t kmin = 0xffffffffu, kmax = 0u;
+    each_candidate([&](int, uint32_t key) {
+      kmin = min(kmin, key);
+      kmax = max(kmax, key);
+    });
+    kmin = wave_min_u32(kmin);
+    kmax = wave_max_u32(kmax);
+    if (lane == 0) {
+      wave_mm[0][w] = kmin;
+      wave_mm[1][w] = kmax;
+    }
+    hist[0][tid] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int x = 0; x < kThreads / kWave; x++) {
+      kmin = min(kmin, wave_mm[0][x]);
+      kmax = max(kmax, wave_mm[1][x]);
+    }
+    const uint32_t diff = kmin ^ kmax;
+    int top = diff ? 31 - __clz((int)diff) : -1;           // highest differing bit
+    pmask = top >= 31 ? 0u : ~((2u << top) - 1u);           // common high bits
+    if (top < 0) pmask = 0xffffffffu;                        // all candidate keys equal
+    prefix = kmin & pmask;
+
+    int hb = 0, certain = 0;
+    while (top >= 0) {
+      const int shift = top >= 7 ? top - 7 : 0;
+      const uint32_t dmask = (1u << (top - shift + 1)) - 1u;   // 1..8 bits
+      hist[hb ^ 1][tid] = 0;                                   // next pass's histogram
+      each_candidate([&](int, uint32_t key) {
+        if ((key & pmask) == prefix) atomicAdd(&hist[hb][(key >> shift) & dmask], 1);
+      });
+      __syncthreads();
+      pick_bin(hb);
+      remaining -= pick[hb][1];
+      certain += pick[hb][1];
+      prefix |= (uint32_t)pick[hb][0] << shift;
+      pmask |= dmask << shift;
+      const bool done = pick[hb][2] == remaining;   // every key with this prefix is chosen
+      top = shift - 1;
+      hb ^= 1;
+      if (done) break;
+      if (top >= 0 && (int64_t)certain * 65536 >= (int64_t)(65536 - opt.tau_q) * Kfree) {
+        // early termination: one pass over the threshold bin's hashes (histogram hb was
+        // cleared during the last pass) orders the rest at random
+        hz = lowbias32(opt.seed ^ lowbias32((uint32_t)(i * a.H + h)));
+        each_candidate([&](int j, uint32_t key) {
+          if ((key & pmask) == prefix) atomicAdd(&hist[hb][lowbias32(hz ^ (uint32_t)j) >> 24], 1);
+        });
+        __syncthreads();
+        pick_bin(hb);
+        remaining -= pick[hb][1];
+        hthr = pick[hb][0];
+        break;
+      }
+    }
+  }
+
+  // Compaction: one scan gives each tied candidate its rank by page index, a second gives each
+  // chosen page its slot.
+  // After an early stop a bin member ranks above the tie class by its hash, else ties.
+  auto hash_cmp = [&](int j) -> int {
+    if (hthr < 0) return 0;
+    const int hv = (int)(lowbias32(hz ^ (uint32_t)j) >> 24);
+    return (hv > hthr) - (hv < hthr);
+  };
+  int n_eq = 0;
+  if (Kfree > 0) {
+    each_candidate([&](int j, uint32_t key) { n_eq += (key & pmask) == prefix && hash_cmp(j) == 0; });
+  }
+  int tot_eq;
+  const int eq_rank = block_incl_scan(n_eq, wave_tot, &tot_eq) - n_eq;
+  // the tie class's chosen members are its `remaining` lowest page indices
+  auto chosen_at = [&](int j, uint32_t key, int& r) -> bool {
+    if (all || is_forced(j, P, nS, nL)) return true;
+    if (Kfree <= 0) return false;
+    const uint32_t mk = key & pmask;
+    if (mk != prefix) return mk > prefix;
+    const int hc = hash_cmp(j);
+    if (hc != 0) return hc > 0;
+    const bool in = r < remaining;
+    r++;
+    return in;
+  };
+  int n_chosen = 0;
+  {
+    int r = eq_rank;
+    for (int j = j_lo; j < j_lo + n_mine; j++) n_chosen += chosen_at(j, Kfree > 0 ? make_key(s[j]) : 0u, r);
+  }
+  int tot_sel;
+  int pos = block_incl_scan(n_chosen, wave_tot, &tot_sel) - n_chosen;
+  {
+    int r = eq_rank;
+    for (int j = j_lo; j < j_lo + n_mine; j++) {
+      if (chosen_at(j, Kfree > 0 ? make_key(s[j]) : 0u, r)) {
+        if (pos < max_sel) out[pos] = j;
+        pos++;
+      }
+    }
+  }
+  for (int m = tot_sel + tid; m < max_sel; m += kThreads) out[m] = -1;
+  if (h == 0 && tid == 0) a.sel_count[i] = min(tot_sel, max_sel);
+}
+
+// Requests of more than kTwoPassMaxPages blocks at the bound.  The bound is often a model's limit and
+// the row far shorter, so a row that fits page slots still takes them.  Rows of up to 8192 / 2000 / 500
+// scores in strides of 20000 / 20000 / 17000 (128 / 512 / 1024 pairs, exact): 59.2 / 18.2 / 8.8 us read
+// again in each pass, 20.0 / 8.9 / 7.5 in slots; with 32 slots for all of them 20.7 / 14.3 / 15.7.
+__global__ __launch_bounds__(kThreads) void topk_long_kernel(const SelArgs a, const TopkOptions opt) {
+  const SelRow row = sel_row(a, (int)blockIdx.x, 1 << 30);
+  if (row.P <= 8 * kThreads) radix_select_slots<kThreads, 8>(a, row, opt);               // uniform
+  else if (row.P <= 32 * kThreads) radix_select_slots<kThreads, 32>(a, row, opt);
+  else radix_select_long(a, row, opt);
 }
 
 // The same exact one-pass selection for requests of at most kWaveMaxPages blocks, by one wave per
@@ -2618,9 +2621,7 @@ void launch_radix(const SelArgs& a, const TopkOptions& opt, hipStream_t stream) 
 // passes; rows past the page slots of both by the general radix kernel.
 void launch_select(const SelArgs& a, const TopkOptions& opt, const AppendStep& ap, hipStream_t stream) {
   if (a.max_pages > kTwoPassMaxPages)
-    hipLaunchKernelGGL(topk_long_kernel, dim3(a.batch * a.H), dim3(kThreads), 0, stream, a.lower, a.H, a.ps, a.r,
-                       a.max_pages, a.stride, a.batch, a.indptr, a.seq_lens, a.items, a.budget, a.n_sink, a.n_local,
-                       a.max_sel, opt, a.sel_pages, a.sel_count);
+    hipLaunchKernelGGL(topk_long_kernel, dim3(a.batch * a.H), dim3(kThreads), 0, stream, a, opt);
   else if (opt.remap != 0 || opt.tau_q != 0) launch_radix(a, opt, stream);
   else launch_bucket<kNoRescore, 0>(a, ap, stream);
 }

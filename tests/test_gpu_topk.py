@@ -42,10 +42,12 @@ def test_topk_select_matches_oracle(dist, tau, remap):
 
 
 @pytest.mark.parametrize("tau,remap", [(0.0, 0), (0.2, 0), (0.2, 1)])
-@pytest.mark.parametrize("stride,n", [(8192, [8192, 4097]), (9000, [9000, 8500])])
+@pytest.mark.parametrize("stride,n", [(8192, [8192, 4097]), (9000, [9000, 8500]), (20000, [20000, 16385]),
+                                      (20000, [8192, 8193]), (20000, [2048, 2049]), (17000, [5, 0]),
+                                      (40000, [40000, 300])])
 def test_topk_select_long_rows(tau, remap, stride, n):
-    """Up to 8192 candidates (32 per thread) keys stay in registers; longer rows recompute them
-    from the scores."""
+    """Up to a stride of 16384, and behind a larger one up to 8192 candidates (8 or 32 per thread), keys
+    stay in registers; longer rows recompute them from the scores."""
     H, B = 2, 2
     sc = synthetic_scores("normal", H, B, stride, seed=7)
     bud = [1000, 700]
