@@ -2404,22 +2404,30 @@ __device__ __forceinline__ double wave_sum_f64(double x) {
   return x;
 }
 
-// NSA: wave w takes the query heads w, w + 4, ... of the group by itself, so a head's max and sum
-// are wave reductions; the exponentials of four heads (a row of up to kFlowTile pages, longer rows
-// tile by tile, with the two neighbours) meet in LDS, where every thread convolves and sums its
-// pages' heads.  Two barriers per four heads where one workgroup per head row needed six each: the
-// kernel waits on its chain of barriers and fp64 exponentials.  Measured (64 requests of 8192 to 32768
-// tokens on pages of 16, 8 KV heads, groups of four): 24.2 -> 13.6 us.
-template <bool kNsa>
+// NSA: the waves take four query heads of the group at a time, one each, so a head's max and sum are
+// wave reductions; where a round has two heads or one, two or four waves share a head's row (kShare: the
+// log2 of the waves per head of every round, -1: by the round) and join their max and sum in LDS.  The
+// exponentials of the round's heads (a row of up to kTile pages, longer rows tile by tile, with the two
+// neighbours) meet in LDS, where every thread convolves and sums its pages' heads.  Two barriers per
+// four heads where one workgroup per head row needed six each: the kernel waits on its chain of barriers
+// and fp64 exponentials, and on the waves in flight, so kTile follows the request bound (a row of 2048
+// pages in registers takes 208 of them) and the LDS the group.  Measured, us with all threads on one head
+// after the other / one wave per head always, 2048 pages at most / now: 512 rows of 2048 pages in groups of
+// 1: 7.4 / 10.0 / 6.5, of 4: 20.1 / 13.7 / 13.6, of 5: 24.1 / 20.5 / 18.0; 1600 rows of 600 pages in groups of
+// 1: 7.4 / 22.6 / 7.0, of 4: 18.5 / 25.3 / 13.5; 128 rows of 8192 pages (16 loads of a lane in flight, where it
+// had one) in groups of 1: 31.8 / 61.9 / 19.1, of 4: 110 / 75.8 / 54.8.
+template <bool kNsa, int kTile, int kShare>
 __global__ __launch_bounds__(kThreads) void flow_kernel(const float* __restrict__ in, float* __restrict__ out, int H,
                                                         int g, int ps, int r, int max_pages, int stride, int batch,
                                                         const int32_t* __restrict__ indptr,
                                                         const int32_t* __restrict__ seq_lens,
                                                         const int32_t* __restrict__ items) {
   constexpr int W = kThreads / kWave;
-  extern __shared__ double e_lds[];                  // NSA: [W][row], row = tile + 2: e_j at 1 + j - tile start
+  extern __shared__ double e_lds[];                  // NSA: [min(g, W)][row], row = tile + 2: e_j at 1 + j - tile start
   __shared__ double inv_of[16];
   __shared__ float max_of[16];
+  __shared__ double part_sum[W];
+  __shared__ float part_max[W];
   const int tid = threadIdx.x;
   const int i = blockIdx.x / H, h = blockIdx.x % H;
   const int P = items ? max(0, min(items[i], stride))
@@ -2435,20 +2443,54 @@ __global__ __launch_bounds__(kThreads) void flow_kernel(const float* __restrict_
     return;
   }
   const int lane = lane_id(), w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int tile = min(max_pages, kFlowTile), row = tile + 2;
-  double* e = e_lds + w * row;
+  const int tile = min(max_pages, kTile), row = tile + 2;
   const bool staged = P <= tile;                     // uniform: one tile, its sums taken on the way
   auto logits = [&](int rr) { return in + ((int64_t)(h * g + rr) * batch + i) * stride; };
+  // A round of n heads: 1 << sh waves share a head's row, 64 pages by 64 pages in turn.
+  auto share = [&](int n) { return kShare >= 0 ? kShare : n >= 3 ? 0 : n == 2 ? 1 : 2; };
+  constexpr int kRound = kTile / kWave >> (kShare > 0 ? kShare : 0);   // a wave's pages of a staged row, by lanes
+  // the max or sum of a head from its waves' parts (behind a barrier when they are several)
+  auto joint = [&](auto x, auto* part, int sh, auto op) {
+    if (sh == 0) return x;                           // uniform
+    if (lane == 0) part[w] = x;
+    __syncthreads();
+    const int w0 = w >> sh << sh;
+    x = part[w0];
+    for (int k = 1; k < 1 << sh; k++) x = op(x, part[w0 + k]);
+    __syncthreads();                                 // part free
+    return x;
+  };
+  auto max_op = [](float a, float b) { return fmaxf(a, b); };
+  auto sum_op = [](double a, double b) { return a + b; };
   if (!staged) {
-    for (int rr = w; rr < g; rr += W) {
-      const float* z = logits(rr);
+    for (int r0 = 0; r0 < g; r0 += W) {
+      const int sh = share(g - r0), rr = r0 + (w >> sh), part = w & ((1 << sh) - 1);
+      const bool mine = rr < g;                      // uniform over the wave
+      const float* z = logits(mine ? rr : 0);
+      const int step = kWave << sh;
+      constexpr int N = 16;                          // loads in flight
       float mx = -INFINITY;
-      for (int j = lane; j < P; j += kWave) mx = fmaxf(mx, z[j]);
-      mx = wave_max_f32(mx);
+      if (mine)
+        for (int j0 = part * kWave + lane; j0 < P; j0 += N * step) {
+          float v[N];
+#pragma unroll
+          for (int x = 0; x < N; x++) v[x] = z[min(j0 + x * step, P - 1)];
+#pragma unroll
+          for (int x = 0; x < N; x++) mx = fmaxf(mx, v[x]);
+        }
+      mx = joint(wave_max_f32(mx), part_max, sh, max_op);
       double l = 0.0;
-      for (int j = lane; j < P; j += kWave) l += exp((double)z[j] - (double)mx);
-      l = wave_sum_f64(l);
-      if (lane == 0) {
+      if (mine)
+        for (int j0 = part * kWave + lane; j0 < P; j0 += N * step) {
+          float v[N];
+#pragma unroll
+          for (int x = 0; x < N; x++) v[x] = z[min(j0 + x * step, P - 1)];
+#pragma unroll
+          for (int x = 0; x < N; x++)
+            if (j0 + x * step < P) l += exp((double)v[x] - (double)mx);
+        }
+      l = joint(wave_sum_f64(l), part_sum, sh, sum_op);
+      if (mine && lane == 0 && part == 0) {
         max_of[rr] = mx;
         inv_of[rr] = 1.0 / l;
       }
@@ -2457,28 +2499,33 @@ __global__ __launch_bounds__(kThreads) void flow_kernel(const float* __restrict_
   }
   for (int t0 = 0; t0 < P; t0 += tile) {
     const int t1 = min(P, t0 + tile);
-    double acc[kFlowTile / kThreads];
+    double acc[kTile / kThreads];
 #pragma unroll
-    for (int x = 0; x < kFlowTile / kThreads; x++) acc[x] = 0.0;
+    for (int x = 0; x < kTile / kThreads; x++) acc[x] = 0.0;
     for (int r0 = 0; r0 < g; r0 += W) {
-      const int rr = r0 + w;
-      if (rr < g) {                                  // uniform over the wave
-        const float* z = logits(rr);
-        if (staged) {
-          float zr[kFlowTile / kWave];
-          float mx = -INFINITY;
+      const int n = min(W, g - r0), sh = share(n), slot = w >> sh, rr = r0 + slot, part = w & ((1 << sh) - 1);
+      const bool mine = slot < n;                    // uniform over the wave
+      const float* z = logits(mine ? rr : 0);
+      const int first = part * kWave + lane, step = kWave << sh;
+      double* e = e_lds + slot * row;
+      if (staged) {
+        float zr[kRound];
+        float mx = -INFINITY;
+        if (mine) {
 #pragma unroll
-          for (int x = 0; x < kFlowTile / kWave; x++)
-            if (x * kWave < P) zr[x] = z[min(x * kWave + lane, P - 1)];   // one round trip
+          for (int x = 0; x < kRound; x++)
+            if (x * step < P) zr[x] = z[min(x * step + first, P - 1)];    // one round trip
 #pragma unroll
-          for (int x = 0; x < kFlowTile / kWave; x++)
-            if (x * kWave < P) mx = fmaxf(mx, zr[x]);
-          mx = wave_max_f32(mx);
-          double l = 0.0;
+          for (int x = 0; x < kRound; x++)
+            if (x * step < P) mx = fmaxf(mx, zr[x]);
+        }
+        mx = joint(wave_max_f32(mx), part_max, sh, max_op);
+        double l = 0.0;
+        if (mine) {
 #pragma unroll
-          for (int x = 0; x < kFlowTile / kWave; x++) {
-            if (x * kWave < P) {
-              const int j = x * kWave + lane;
+          for (int x = 0; x < kRound; x++) {
+            if (x * step < P) {
+              const int j = x * step + first;
               const double v = exp((double)zr[x] - (double)mx);
               if (j < P) {
                 e[1 + j] = v;
@@ -2486,21 +2533,20 @@ __global__ __launch_bounds__(kThreads) void flow_kernel(const float* __restrict_
               }
             }
           }
-          l = wave_sum_f64(l);
-          if (lane == 0) inv_of[rr] = 1.0 / l;
-        } else {
-          const double mx = (double)max_of[rr];
-          for (int j = max(0, t0 - 1) + lane; j < min(P, t1 + 1); j += kWave) e[1 + j - t0] = exp((double)z[j] - mx);
         }
-        if (lane == 0) {                             // zero padding at the ends of the row
-          if (t0 == 0) e[0] = 0.0;
-          if (t1 == P) e[1 + P - t0] = 0.0;
-        }
+        l = joint(wave_sum_f64(l), part_sum, sh, sum_op);
+        if (mine && lane == 0 && part == 0) inv_of[rr] = 1.0 / l;
+      } else if (mine) {
+        const double mx = (double)max_of[rr];
+        for (int j = max(0, t0 - 1) + first; j < min(P, t1 + 1); j += step) e[1 + j - t0] = exp((double)z[j] - mx);
+      }
+      if (mine && lane == 0 && part == 0) {          // zero padding at the ends of the row
+        if (t0 == 0) e[0] = 0.0;
+        if (t1 == P) e[1 + P - t0] = 0.0;
       }
       __syncthreads();
-      const int n = min(W, g - r0);
 #pragma unroll
-      for (int x = 0; x < kFlowTile / kThreads; x++) {
+      for (int x = 0; x < kTile / kThreads; x++) {
         const int j = t0 + x * kThreads + tid;
         if (j < t1) {
           const double* q = e_lds + 1 + j - t0;
@@ -2510,7 +2556,7 @@ __global__ __launch_bounds__(kThreads) void flow_kernel(const float* __restrict_
       __syncthreads();                               // e free for the next heads or tile
     }
 #pragma unroll
-    for (int x = 0; x < kFlowTile / kThreads; x++) {
+    for (int x = 0; x < kTile / kThreads; x++) {
       const int j = t0 + x * kThreads + tid;
       if (j < t1) y[j] = (float)acc[x];
     }
@@ -2843,13 +2889,28 @@ hipError_t launch_score_flow(int kind, const float* in, float* out, int stride, 
                              const int32_t* items, int ps, int r, int max_pages, const int32_t* indptr,
                              const int32_t* seq_lens, hipStream_t stream) {
   if (batch == 0) return hipSuccess;
-  if (kind == kAbiNsa)
-    hipLaunchKernelGGL(flow_kernel<true>, dim3(batch * H), dim3(kThreads),
-                       sizeof(double) * (kThreads / kWave) * (std::min(max_pages, kFlowTile) + 2), stream, in, out, H,
-                       Hq / H, ps, r, max_pages, stride, batch, indptr, seq_lens, items);
-  else
-    hipLaunchKernelGGL(flow_kernel<false>, dim3(batch * H), dim3(kThreads), 0, stream, in, out, H, Hq / H, ps, r,
-                       max_pages, stride, batch, indptr, seq_lens, items);
+  if (kind == kAbiNsa) {
+    const int rows = std::min(Hq / H, kThreads / kWave);
+    auto launch = [&](auto tile, auto share) {
+      constexpr int T = decltype(tile)::value, S = decltype(share)::value;
+      hipLaunchKernelGGL((flow_kernel<true, T, S>), dim3(batch * H), dim3(kThreads),
+                         sizeof(double) * rows * (std::min(max_pages, T) + 2), stream, in, out, H, Hq / H, ps, r,
+                         max_pages, stride, batch, indptr, seq_lens, items);
+    };
+    auto with_tile = [&](auto share) {
+      if (max_pages <= kFlowTile / 4) launch(std::integral_constant<int, kFlowTile / 4>{}, share);
+      else if (max_pages <= kFlowTile / 2) launch(std::integral_constant<int, kFlowTile / 2>{}, share);
+      else launch(std::integral_constant<int, kFlowTile>{}, share);
+    };
+    const int g = Hq / H;
+    if (g == 1) with_tile(std::integral_constant<int, 2>{});
+    else if (g == 2) with_tile(std::integral_constant<int, 1>{});
+    else if (g % 4 == 0 || g % 4 == 3) with_tile(std::integral_constant<int, 0>{});
+    else with_tile(std::integral_constant<int, -1>{});
+  } else {
+    hipLaunchKernelGGL((flow_kernel<false, kThreads, 0>), dim3(batch * H), dim3(kThreads), 0, stream, in, out, H, Hq / H,
+                       ps, r, max_pages, stride, batch, indptr, seq_lens, items);
+  }
   return hipGetLastError();
 }
 

@@ -40,8 +40,8 @@ def test_head_logits(D, H, g, block):
         assert np.isnan(got[:, i, n:]).all()
 
 
-@pytest.mark.parametrize("g", [1, 3, 4, 5, 16])
-@pytest.mark.parametrize("P", [1, 63, 65, 2047, 2048, 2049, 4096, 4099])
+@pytest.mark.parametrize("g", [1, 2, 3, 4, 5, 6, 16])
+@pytest.mark.parametrize("P", [1, 63, 65, 511, 513, 1024, 1025, 2047, 2048, 2049, 4096, 4099])
 def test_nsa_flow_rows(P, g):
     H, B = 2, 2
     n = np.array([P, max(1, P // 2)], np.int32)
