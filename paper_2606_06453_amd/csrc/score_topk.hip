@@ -1219,8 +1219,8 @@ struct SlotWords {
     lo = mine ? (uint32_t)m : lo;
     hi = mine ? (uint32_t)(m >> 32) : hi;
   }
-  __device__ __forceinline__ void add(int x, uint64_t m) {      // into slot x's word
-    const bool mine = lane_id() == x;
+  __device__ __forceinline__ void add(int x, uint64_t m, int lane = lane_id()) {   // into slot x's word
+    const bool mine = lane == x;
     lo |= mine ? (uint32_t)m : 0u;
     hi |= mine ? (uint32_t)(m >> 32) : 0u;
   }
@@ -1548,8 +1548,9 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(D > 128 ? 2 :
     int need = s.Kfree, n_und;
 #pragma clang loop unroll(disable)
     for (int round = 0;; round++) {
-      int Pr = P;                                    // the slots' tests are made in the round: kept around
+      int Pr = P, ln = lane;                         // the slots' tests are made in the round: kept around
       asm volatile("" : "+s"(Pr));                   // the loop they spill
+      asm volatile("" : "+v"(ln));
       const float origin = lo_min, scale = bin_scale(lo_min, hi_max);
       // NaN bounds (and any with scale 0) fall into bin 0
       auto bin_of = [&](float x) { return (int)fminf(fmaxf((x - origin) * scale, 0.f), (float)(kBins - 1)); };
@@ -1588,7 +1589,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(D > 128 ? 2 :
           const uint64_t mi = __ballot(in);
           n_in += __popcll(mi);
           n_mine += __popcll(mu[x]);
-          sw.add(x, mi);
+          sw.add(x, mi, ln);
         }
       }
       sw.store(words, w, Pr);
@@ -1861,7 +1862,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(D > 128 ? 2 :
 // of up to 3000 scores 19.3 -> 8.8.
 // ------------------------------------------------------------------------------------
 template <int T, int K>
-__device__ __forceinline__ void radix_select_slots(const SelArgs& a, const SelRow& s, const TopkOptions& opt) {
+__device__ __forceinline__ void radix_select_slots(const SelArgs a, const SelRow s, const TopkOptions opt) {
   using S = SelShape<T, K>;
   __shared__ __align__(16) int hist[3][256];
   __shared__ uint2 words[S::kWords];              // chosen pages
