@@ -584,8 +584,9 @@ def test_two_pass_near_ties(n_pages, noise):
 
 @pytest.mark.parametrize("kind", [O.MEAN_DOT, O.QUEST, O.MAX_DOT, O.NSA, O.MEAN_DOT_SMOOTH, O.MEAN_DOT_CONTENT])
 def test_requests_longer_than_4096_pages(kind):
-    """Past 4096 pages per request the selection runs the general radix kernel (and MEAN_DOT
-    ignores the bf16 copy); a second, short request keeps the batch ragged."""
+    """Past 4096 pages per request the bucketed selection holds eight or more pages per thread (at
+    these sizes Quest in two passes, the block mean in one); a second, short request keeps the batch
+    ragged."""
     from tests._problems import random_problem
     lens = [16 * 4500 + 7, 16 * 37]
     pb = random_problem(900 + kind, lens, Hq=4, H=2, D=64, ps=16)

@@ -57,8 +57,6 @@ def _select(scores, lens, budget, kind, two_pass, n_sink, n_local, max_sel):
                                    (8193, 2, 1), (16384, 2, 1), (16385, 2, 1)])
 @pytest.mark.parametrize("kind,two_pass", [(vx.MAX_DOT, False), (vx.MEAN_DOT, True), (vx.QUEST, True)])
 def test_selection_shapes(kind, two_pass, P, B, H, dist):
-    if dist == "coarse" and kind != vx.MAX_DOT:
-        pytest.skip("an infinite bf16 Mean or envelope times a zero query channel has no finite bound")
     rng = np.random.default_rng(P + B)
     scores = _scores((H, B, P), dist, rng)
     pages = rng.integers(P // 2, P + 1, B).astype(np.int32)

@@ -1,11 +1,10 @@
 """vx_append_score_topk (the decode step's append inside the top-K launch) against the two calls
 it stands for, vx_kv_append_summarize then vx_page_score_topk, on the GPU: the caches, every
-summary buffer and the selection must come out bit for bit the same.  Covered: the bucketed
-selection paths that carry the append (two-pass block mean, one-pass block mean and Max,
-two-pass Quest), the MLA latent (its 64 x 576 and 32 x 576 blocks refreshed by workgroups of
-their own in the one-pass selection launch, also with an fp8 latent), an fp8 cache, blocks below
-the page size, and the cases that append first instead (n_local = 0, NSA, an approximate
-selection, a 64 x 576 block on the two-pass path)."""
+summary buffer and the selection must come out bit for bit the same.  Covered: the selections
+whose launch carries the append in workgroups of its own (two-pass block mean, one-pass block mean
+and Max, two-pass Quest; the MLA latent's 64 x 576 and 32 x 576 blocks, also with an fp8 latent), at
+every workgroup size of the selection, an fp8 cache, blocks below the page size, and the cases that
+append first instead (n_local = 0, NSA, an approximate selection, more than 16384 blocks)."""
 import pytest
 import torch
 
@@ -22,11 +21,11 @@ CASES = [
     ("max_one_pass", 32, 0, 128, 8, 2, O.MAX_DOT, False, None, 1, 0.0),
     ("quest_two_pass", 16, 0, 128, 8, 2, O.QUEST, False, None, 2, 0.0),
     ("rectified", 32, 0, 64, 8, 2, O.QUEST_RECTIFIED, False, None, 2, 0.0),
-    ("mla_latent", 64, 0, 576, 16, 1, O.MEAN_DOT, True, None, 2, 0.0),   # appends first (64 x 576, two passes)
-    ("mla_latent_one_pass", 64, 0, 576, 16, 1, O.MEAN_DOT, False, None, 2, 0.0),   # append workgroups
+    ("mla_latent", 64, 0, 576, 16, 1, O.MEAN_DOT, True, None, 2, 0.0),
+    ("mla_latent_one_pass", 64, 0, 576, 16, 1, O.MEAN_DOT, False, None, 2, 0.0),
     ("mla_latent_fp8", 64, 0, 576, 16, 1, O.MEAN_DOT, False, torch.float8_e5m2, 1, 0.0),
     ("mla_latent_pages_of_32", 32, 0, 576, 16, 1, O.MEAN_DOT, False, None, 2, 0.0),
-    ("pages_of_64", 64, 0, 128, 8, 2, O.MEAN_DOT, True, None, 2, 0.0),   # 64 x 128: still fused
+    ("pages_of_64", 64, 0, 128, 8, 2, O.MEAN_DOT, True, None, 2, 0.0),
     ("fp8_e4m3", 16, 0, 128, 8, 2, O.MEAN_DOT, True, torch.float8_e4m3fn, 2, 0.0),
     ("blocks_of_16", 32, 16, 128, 8, 2, O.QUEST, False, None, 2, 0.0),
     ("no_local_window", 16, 0, 128, 8, 2, O.MEAN_DOT, True, None, 0, 0.0),
@@ -54,10 +53,41 @@ def _state(pb, k, v, ks, vs, bs, H, D):
 
 @pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
 def test_append_inside_selection_equals_separate_calls(case):
+    ps, r = case[1], case[1] // case[2] if case[2] else 1
+    lens = [ps * 40 + 3, ps * 9 + 1, ps * 3, 7, ps * 25 + ps // 2, ps * 14]
+    _fused_equals_separate(case, lens, [12 * r, 5 * r, 4 * r, 1, 20 * r, 9 * r], 24 * r)
+
+
+# request bound in pages, further one-page requests (with them the pairs fill the chip)
+LARGE = [
+    (("mean_256_threads", 16, 0, 64, 4, 2, O.MEAN_DOT, True, None, 1, 0.0), 700, 0),
+    (("quest_512_threads", 16, 0, 128, 8, 2, O.QUEST, False, None, 1, 0.0), 1500, 0),
+    (("max_512_threads_16_heads", 16, 0, 64, 16, 16, O.MAX_DOT, False, torch.float8_e4m3fn, 1, 0.0), 1100, 0),
+    (("mean_1024_threads", 16, 0, 128, 6, 2, O.MEAN_DOT, True, None, 2, 0.0), 2100, 0),
+    (("max_512_threads_8_slots", 16, 0, 64, 8, 8, O.MAX_DOT, False, None, 1, 0.0), 2100, 30),
+    (("quest_256_threads_16_slots", 16, 0, 64, 8, 8, O.QUEST, False, None, 1, 0.0), 2100, 70),
+    (("quest_1024_threads_8_slots", 32, 16, 64, 8, 2, O.QUEST, False, torch.float8_e5m2, 1, 0.0), 2100, 0),
+    (("mean_1024_threads_16_slots", 16, 0, 64, 4, 2, O.MEAN_DOT, True, None, 1, 0.0), 8300, 0),
+    (("max_past_the_slots", 16, 0, 64, 2, 1, O.MAX_DOT, False, None, 1, 0.0), 16500, 0),
+    (("latent_512_threads", 16, 0, 576, 16, 1, O.MEAN_DOT, True, None, 1, 0.0), 1100, 0),
+    (("latent_512_threads_16_slots", 16, 0, 576, 16, 1, O.MEAN_DOT, True, None, 1, 0.0), 4200, 0),
+    (("latent_1024_threads_one_pass", 16, 0, 576, 16, 1, O.MEAN_DOT, False, None, 1, 0.0), 2100, 0),
+]
+
+
+@pytest.mark.parametrize("case,pages,more", LARGE, ids=[c[0][0] for c in LARGE])
+def test_append_inside_large_selections(case, pages, more):
+    """The same at the selection's workgroup sizes, where the append's tasks fill part of a workgroup, one or
+    several; the appended token starts a block, ends one or lies within."""
+    ps, r = case[1], case[1] // case[2] if case[2] else 1
+    lens = [ps * (pages - 1) + 1, ps * (pages // 2), ps * (pages // 3) + 5, 2] + [ps] * more
+    _fused_equals_separate(case, lens, [r * pages // 8, 60 * r, 7 * r, 1] + [1] * more, max(60, pages // 8) * r)
+
+
+def _fused_equals_separate(case, lens, budget, max_sel):
     name, ps, bs, D, Hq, H, kind, two_pass, fp8, n_local, tau = case
     mla = D == 576
     r = ps // bs if bs else 1
-    lens = [ps * 40 + 3, ps * 9 + 1, ps * 3, 7, ps * 25 + ps // 2, ps * 14]
     pb = random_problem(2200 + ps + D + Hq + n_local, lens, Hq=Hq, H=H, D=D, ps=ps, Dv=512 if mla else None,
                         alias_v=mla, extra_pages=4)
     ks, vs = 1.0, 1.0
@@ -65,9 +95,8 @@ def test_append_inside_selection_equals_separate_calls(case):
         ks, vs = 0.021, 0.0377
         pb = fp8_problem(pb, fp8, ks, vs)
     k, v, kn, vn = strip_last_token(pb, 2201)
-    budget = torch.tensor([12 * r, 5 * r, 4 * r, 1, 20 * r, 9 * r], dtype=torch.int32).cuda()
-    max_sel, n_sink = 24 * r, 1 * r
-    nl = n_local * r
+    budget = torch.tensor(budget, dtype=torch.int32).cuda()
+    n_sink, nl = r, n_local * r
     q = pb.q.cuda()
     opt = vx.topk_options(tolerate_ratio=tau, seed=5) if tau else None
     outs = []
