@@ -8,10 +8,10 @@
 // instruction reads whole rows of several slices.  HBM-bound: it reads page_size*D*2 bytes
 // (page_size*D for an fp8 cache) and writes D*(4 + 2 + 2) bytes per (page, head).  A full pass
 // streams both ways (non-temporal loads and stores), forms only the kinds of summary asked for and
-// gives a workgroup one round of tasks: 16 prompts of 16k to 32k tokens on pages of 16, Mean and its
-// bf16 copy (969 MB), 205 -> 189 us; 16 prompts of 131072 tokens on pages of 32, Max and Min (4.6
-// GB), 967 -> 820 us.  (Of the first 16 us: wider batches and non-temporal loads 10, stores 6; with
-// four rounds of tasks per workgroup 193 us, with sixteen 212.)
+// gives a workgroup one round of tasks, two in large launches over blocks of 16 (below): 16 prompts of
+// 16k to 32k tokens on pages of 16, Mean and its bf16 copy (969 MB), 205 -> 189 us; 16 prompts of 131072
+// tokens on pages of 32, Max and Min (4.6 GB), 967 -> 820 us.  (Of the first 16 us: wider batches and
+// non-temporal loads 10, stores 6; with four rounds of tasks per workgroup 193 us, with sixteen 212.)
 // fp8 caches: each code is converted exactly to fp32 and multiplied by the K scale (one fp32
 // rounding), which is the cache value the summaries are taken over.
 //
@@ -123,12 +123,14 @@ hipError_t launch_summarize(const Geometry& g, const int32_t* first_page, float*
     // Blocks of 16 tokens are one round trip per task.  Once a launch is many rounds of workgroups
     // deep, two rounds of tasks per workgroup halve what each spends on its request's geometry (and
     // the workgroups past the ends of short requests); a small launch needs the workgroups, and a
-    // bf16 Mean's stores keep them busy.  At one / two rounds: 16 prompts of 16k to 32k tokens, E4M3
-    // Mean 127.1 / 118.5 us, envelope 115.0 / 109.0, bf16 Max 174.2 / 170.5, envelope 182.7 / 180.8,
-    // Mean 188.3 / 190.2; one prompt of 4000 tokens 5.1 / 7.4; blocks of 64, E4M3 89.0 / 93.9.
+    // bf16 Mean's stores keep them busy.  us at one / two rounds, by workgroups of one round per CU: 64
+    // (16 prompts of 16k to 32k tokens) E4M3 Mean 129.7 / 121.1, envelope 116.1 / 109.9, bf16 Max 176.2 /
+    // 173.0, envelope 184.2 / 182.9, Mean 189.6 / 193.0; 128 (16 of 4k to 64k, lognormal) E4M3 Mean 120.7 /
+    // 107.5, bf16 Max 153.9 / 149.3, Mean 162.4 / 164.6; 32 (32 of 1k to 8k, lognormal) E4M3 Mean 38.9 / 39.7,
+    // bf16 Max 48.0 / 49.5; 16 (64 of 256 to 2048) 30.6 / 34.7, 35.0 / 39.2.  Blocks of 64, E4M3 89.0 / 93.9.
     const int ppb1 = tasks_per_page >= kThreads ? 1 : kThreads / tasks_per_page;
     const long long wgs = ((long long)g.max_pages + ppb1 - 1) / ppb1 * g.batch;
-    const bool two = g.bs <= 16 && (g.kv_dtype != kKvBf16 || (!mean && !mean_bf)) && wgs >= 32LL * device_cus();
+    const bool two = g.bs <= 16 && (g.kv_dtype != kKvBf16 || (!mean && !mean_bf)) && wgs >= 48LL * device_cus();
     const int ppb = two ? 2 * ppb1 : ppb1;
     int gx = (g.max_pages + ppb - 1) / ppb;
     if (gx < 1) gx = 1;
