@@ -1162,10 +1162,10 @@ __device__ __forceinline__ void radix_advance(RadixState& r, const int* pick) {
 // holds pages t, t + T, ..., so 64 consecutive pages lie in one wave's lanes of one slot, a ballot
 // is a 64-bit word of page flags, and the words in slot and wave order are the pages in ascending
 // order.  The chosen set is those words in LDS; compacting it takes one wave-wide prefix over
-// their counts, which every wave forms for itself.  What bounds these kernels is latency: a chain
-// of dependent round trips (geometry, bound rows, re-scored summaries) and barriers at few
-// instructions each, so slots past the request's pages are skipped by uniform branches and the
-// shape (T, K) follows the request bound.
+// their counts, which every wave forms for itself.  A few pairs wait for a chain of dependent round
+// trips (geometry, bound rows, re-scored summaries) and barriers; a chip full of pairs is bound by
+// instruction issue.  So slots past the request's pages are skipped by uniform branches, and the
+// shape (T, K) follows the request bound and the number of pairs.
 // ------------------------------------------------------------------------------------
 template <int T, int K>
 struct SelShape {
@@ -1380,9 +1380,10 @@ __device__ __forceinline__ void append_tasks(const AppendStep& ap, int a, int H,
 //   otherwise undecided: ranked by its exact score; the best K - |in| of them by (score desc,
 //   page asc) complete the set.
 // B is non-decreasing, so the classification is as rigorous on bins as on the floats.  kBins bins are
-// enough for the block mean, whose bounds span about nine of them on spread-out scores; the envelope
-// bounds are some 25 times narrower than a bin, which then leaves the two to six pages that share
-// the threshold's, and one block that scores far above the others widens the bins for all.  So
+// enough for the block mean, whose bounds leave the thresholds some three bins apart on spread-out
+// scores (22 pages undecided on rows of 512 to 2048, 20 with 65536 bins); the envelope bounds are some 25
+// times narrower than a bin, which leaves two to eight pages of the threshold's own to most rows of
+// 4096, and one block that scores far above the others widens the bins for all.  So
 // while both thresholds lie in one bin or in neighbours and more pages are undecided than one round of
 // re-scoring takes, the undecided are binned again, between the extremes of the thresholds' own bins.
 // Whole call, 64 pairs of 8192 blocks, one block scaled by 1 / 300 / 10^6: Quest 63.4 / 85.0 / 305 us with
@@ -1400,9 +1401,8 @@ __device__ __forceinline__ void append_tasks(const AppendStep& ap, int a, int H,
 // is re-scored, in batches whose rows and page ids load ahead of their use.  One workgroup then reads
 // all of its row: 64 pairs of 8192 blocks whose Means differ by 2 % of their size, whole call 166 us with
 // two dependent pages per lane row at a time, 145 so; 16 pairs of 16384 blocks 306 / 228.
-// What bounds it is instruction issue (the active-instruction counter covers 8 of the 12 us on 512
-// pairs) behind a chain of five round trips: few operations per page slot matter more than their
-// latency.  Kernel trace, against 16-bit bucket keys found in two 256-bin passes by four waves of 16
+// On 512 pairs instruction issue bounds it (the active-instruction counter covers 8 of the 12 us)
+// behind a chain of five round trips.  Kernel trace, against 16-bit bucket keys found in two 256-bin passes by four waves of 16
 // slots per thread, each appending its own head first: 512 pairs of up to 2048 pages, two-pass block
 // mean 17.3 -> 12.6 us; 128 pairs of 4096 pages, two-pass Quest 15.9 -> 11.3; 1024 pairs of up to
 // 4096 pages, Max 16.9 -> 12.1; 512 pairs of NSA scores 28.7 -> 12.5; 32 pairs of 2048 pages 10.1 ->
@@ -2648,7 +2648,12 @@ void launch_bucket(const SelArgs& a, const AppendStep& ap, hipStream_t stream) {
   }
 }
 
-// The radix selection's shape, as the bucketed one's.
+// The radix selection's shape: as the bucketed one's, but long rows take 512 threads once there is more
+// than a pair per CU.  us a call (remapped, tau 0.2) at 32 / 128 / 512 / 1024 pairs, rows of up to 1000:
+// 256 threads 4.9 / 5.1 / 5.7 / 7.3, 512 4.9 / 5.1 / 6.4 / 9.0; 2000: 512 x 4 slots 5.8 / 5.6 / 7.7 / 10.8, 256 x
+// 8 6.7 / 6.7 / 8.1 / 10.1; 4000: 1024 x 4 7.8 / 8.0 / 11.3 / 19.9, 512 x 8 8.1 / 8.2 / 10.7 / 16.8, 256 x 16 10.9 /
+// 11.3 / 12.5 / 17.0; 8000: 1024 x 8 11.5 / 11.6 / 20.1 / 38.1, 512 x 16 13.0 / 13.1 / 17.8 / 28.3, 256 x 32 19.6 /
+// 19.7 / 22.3 / 30.3; 16000: 1024 x 16 18.1 / 19.1 / 35.5 / 67.4, 512 x 32 20.2 / 21.3 / 30.2 / 57.0.
 template <int T, int K>
 void launch_radix_shape(const SelArgs& a, const TopkOptions& opt, hipStream_t stream) {
   hipLaunchKernelGGL((topk_radix_kernel<T, K>), dim3(a.batch * a.H), dim3(T), 0, stream, a, opt);
@@ -2657,11 +2662,14 @@ void launch_radix(const SelArgs& a, const TopkOptions& opt, hipStream_t stream) 
   const long long pairs = (long long)a.batch * a.H, cus = device_cus();
   if (a.max_pages <= 1024) launch_radix_shape<256, 4>(a, opt, stream);
   else if (a.max_pages <= 2048 && pairs <= 2 * cus) launch_radix_shape<512, 4>(a, opt, stream);
+  else if (a.max_pages <= 2048) launch_radix_shape<256, 8>(a, opt, stream);
   else if (a.max_pages <= 4096 && 2 * pairs <= cus) launch_radix_shape<1024, 4>(a, opt, stream);
   else if (a.max_pages <= 4096 && pairs <= 2 * cus) launch_radix_shape<512, 8>(a, opt, stream);
   else if (a.max_pages <= 4096) launch_radix_shape<256, 16>(a, opt, stream);
-  else if (a.max_pages <= 8192) launch_radix_shape<1024, 8>(a, opt, stream);
-  else launch_radix_shape<1024, 16>(a, opt, stream);
+  else if (a.max_pages <= 8192 && pairs <= cus) launch_radix_shape<1024, 8>(a, opt, stream);
+  else if (a.max_pages <= 8192) launch_radix_shape<512, 16>(a, opt, stream);
+  else if (pairs <= cus) launch_radix_shape<1024, 16>(a, opt, stream);
+  else launch_radix_shape<512, 32>(a, opt, stream);
 }
 
 // Selection from scores in a.lower: exact and unmapped by the bucketed kernel, else by radix

@@ -58,7 +58,7 @@ hipError_t launch_summarize(const Geometry& g, const int32_t* first_page, float*
 hipError_t launch_kv_append_summarize(const Geometry& g, const void* k_new, const void* v_new, float* mean,
                                       uint16_t* mean_bf, uint16_t* maxo, uint16_t* mino, hipStream_t stream);
 
-// mean_bf != nullptr (MEAN_DOT only, max_pages <= kTwoPassMaxPages) selects the exact
+// mean_bf != nullptr (MEAN_DOT or MEAN_DOT_CONTENT, max_pages <= kTwoPassMaxPages) selects the exact
 // two-pass path: a bounded first pass over the bf16 means, then fp32 re-scoring of the
 // undecided pages.
 constexpr int kTwoPassMaxPages = 16384;

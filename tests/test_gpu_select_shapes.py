@@ -74,7 +74,8 @@ def test_selection_shapes(kind, two_pass, P, B, H, dist):
 @pytest.mark.parametrize("dist", ["normal", "equal", "skewed", "coarse"])
 @pytest.mark.parametrize("tau,remap", [(0.0, 0), (0.0, 1), (0.2, 0), (0.2, 1)])
 @pytest.mark.parametrize("P,B,H", [(1, 2, 1), (500, 3, 2), (1025, 3, 2), (2048, 40, 16), (2049, 2, 2), (4096, 5, 4),
-                                   (4096, 33, 16), (4097, 3, 2), (8193, 2, 1), (16384, 2, 1), (16385, 2, 1)])
+                                   (4096, 33, 16), (4097, 3, 2), (8193, 2, 1), (16384, 2, 1), (16385, 2, 1),
+                                   (5000, 33, 8), (9000, 33, 8)])
 def test_radix_selection_shapes(P, B, H, tau, remap, dist):
     """vx_topk_select at the same edges, its options included, over rows of any alignment."""
     rng = np.random.default_rng(P + B)
