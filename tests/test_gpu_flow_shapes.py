@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("D,H,g", [(64, 1, 1), (128, 1, 5), (64, 2, 4), (128, 2, 16), (128, 4, 3), (64, 8, 8),
-                                   (128, 8, 9), (128, 16, 2), (64, 16, 13)])
+                                   (128, 8, 9), (128, 16, 2), (64, 16, 13), (128, 8, 16), (64, 16, 16)])
 @pytest.mark.parametrize("block", [0, 16])
 def test_head_logits(D, H, g, block):
     ps = 32
