@@ -1423,9 +1423,11 @@ __device__ __forceinline__ float bin_scale(float lo, float hi) {
 // otherwise take for the append workgroups' divisions cost the selection its residency, and a grid
 // that is not resident at once leaves the dispatcher in the middle of a round over the CUs, which
 // upsets the decode launch's pairing of long and short requests per CU (1024 pairs: decode 36.5 us
-// after a selection at four waves per SIMD, 34.2 us at six).
+// after a selection at four waves per SIMD, 34.2 us at six).  1024 threads are alone on a CU at either;
+// the block mean's take four for its batches of four rows, the envelope kinds' were slower so (64
+// pairs of up to 8192 blocks with the append, kernel trace: 12.6 against 12.4 us).
 template <int RK, int D, int T, int K>
-__global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(D > 128 ? 2 : (T > 512 && RK != kNoRescore) || (K > 8 && (T > 256 || RK != kNoRescore)) ? 4 : 6))) void topk_bucket_kernel(const SelArgs a, const AppendStep ap) {
+__global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(D > 128 ? 2 : (T > 512 && RK == kMeanDot) || (K > 8 && (T > 256 || RK != kNoRescore)) ? 4 : 6))) void topk_bucket_kernel(const SelArgs a, const AppendStep ap) {
   using S = SelShape<T, K>;
   constexpr bool kMeanRescore = RK == kMeanDot;
   constexpr bool kEnvRescore = is_env(RK);
@@ -1495,7 +1497,8 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(D > 128 ? 2 :
           if constexpr (kRescore) hi_max = fmaxf(hi_max, uf[x]);
           else hi_max = fmaxf(hi_max, lf[x]);
         }
-        sw.put(x, __ballot(x * T + tid < P && !cand));   // forced pages are chosen
+        const int j0 = x * T + kWave * w;            // forced pages are chosen: in words at the row's ends
+        if (j0 < s.nS || j0 + kWave > P - s.nL) sw.put(x, __ballot(x * T + tid < P && !cand));   // uniform
       }
     }
     if constexpr (kMeanRescore) {
