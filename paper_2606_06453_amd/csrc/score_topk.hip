@@ -1386,8 +1386,8 @@ __device__ __forceinline__ void append_tasks(const AppendStep& ap, int a, int H,
 // 4096, and one block that scores far above the others widens the bins for all.  So
 // while both thresholds lie in one bin or in neighbours and more pages are undecided than one round of
 // re-scoring takes, the undecided are binned again, between the extremes of the thresholds' own bins.
-// Whole call, 64 pairs of 8192 blocks, one block scaled by 1 / 300 / 10^6: Quest 63.4 / 85.0 / 305 us with
-// one histogram, 63.7 / 72.3 / 82 so; block mean 39.1 / 48.9 / 176 and 39.2 / 46.7 / 57.  Refining fewer
+// Whole call, 64 pairs of 8192 blocks, one block scaled by 1 / 300 / 10^6: Quest 63.7 / 85.1 / 305 us with
+// one histogram, 63.0 / 71.7 / 81 so; block mean 39.2 / 49.2 / 176 and 39.1 / 46.6 / 57.  Refining fewer
 // pages than that costs more than re-scoring them (Quest 68.4 us without an outlier, 52.7 instead of
 // 45.9 on 16 pairs of 16384 blocks).
 // RK = kMeanDot: the two-pass block-mean selection (bounds in, fp32 Mean rows of D channels for
@@ -1400,7 +1400,7 @@ __device__ __forceinline__ void append_tasks(const AppendStep& ap, int a, int H,
 // keys.  More than kMaxUndecided pages to re-score (bounds wider than the scores' spread): every page
 // is re-scored, in batches whose rows and page ids load ahead of their use.  One workgroup then reads
 // all of its row: 64 pairs of 8192 blocks whose Means differ by 2 % of their size, whole call 166 us with
-// two dependent pages per lane row at a time, 145 so; 16 pairs of 16384 blocks 306 / 228.
+// two dependent pages per lane row at a time, 144 so; 16 pairs of 16384 blocks 306 / 227.
 // On 512 pairs instruction issue bounds it (the active-instruction counter covers 8 of the 12 us)
 // behind a chain of five round trips.  Kernel trace, against 16-bit bucket keys found in two 256-bin passes by four waves of 16
 // slots per thread, each appending its own head first: 512 pairs of up to 2048 pages, two-pass block
@@ -1415,8 +1415,9 @@ constexpr int kBinRounds = 4;          // histograms of the re-scored kinds at m
 // fp32 is halved first (x - lo may then be infinite: the last bin).
 __device__ __forceinline__ float bin_scale(float lo, float hi) {
   const float span = hi - lo;
-  if (!(span > 0.f)) return 0.f;
-  return span < INFINITY ? (float)kBins / span : (float)(kBins / 2) / (0.5f * hi - 0.5f * lo);
+  const bool fits = span < INFINITY;
+  const float scale = (fits ? (float)kBins : (float)(kBins / 2)) / (fits ? span : 0.5f * hi - 0.5f * lo);
+  return span > 0.f ? scale : 0.f;
 }
 
 // Six waves per SIMD (80 VGPRs) where the re-scoring allows it: the registers the compiler would
@@ -1492,13 +1493,15 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(D > 128 ? 2 :
       if (x * T < P) {
         const bool cand = is_cand(x * T + tid);
         if (cand) {
-          um |= 1u << x;
+          if constexpr (kRescore) um |= 1u << x;
           lo_min = fminf(lo_min, lf[x]);
           if constexpr (kRescore) hi_max = fmaxf(hi_max, uf[x]);
           else hi_max = fmaxf(hi_max, lf[x]);
         }
-        const int j0 = x * T + kWave * w;            // forced pages are chosen: in words at the row's ends
-        if (j0 < s.nS || j0 + kWave > P - s.nL) sw.put(x, __ballot(x * T + tid < P && !cand));   // uniform
+        if constexpr (kRescore) {
+          const int j0 = x * T + kWave * w;          // forced pages are chosen: in words at the row's ends
+          if (j0 < s.nS || j0 + kWave > P - s.nL) sw.put(x, __ballot(x * T + tid < P && !cand));   // uniform
+        }
       }
     }
     if constexpr (kMeanRescore) {
@@ -1548,12 +1551,19 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(D > 128 ? 2 :
         qbar[c] = c < a.qdims ? finish_qbar_one(acc, g) : 0.0;
       }
     }
+    // exact scores take one round, which knows the candidates by their pages
+    auto pending = [&](int x) -> bool {
+      if constexpr (kRescore) return (um >> x) & 1u;
+      else return is_cand(x * T + tid);
+    };
     int need = s.Kfree, n_und;
 #pragma clang loop unroll(disable)
     for (int round = 0;; round++) {
-      int Pr = P, ln = lane;                         // the slots' tests are made in the round: kept around
-      asm volatile("" : "+s"(Pr));                   // the loop they spill
-      asm volatile("" : "+v"(ln));
+      int Pr = P, ln = lane;
+      if constexpr (kRescore) {                      // the slots' tests are made in the round: kept around
+        asm volatile("" : "+s"(Pr));                 // the loop they spill
+        asm volatile("" : "+v"(ln));
+      }
       const float origin = lo_min, scale = bin_scale(lo_min, hi_max);
       // NaN bounds (and any with scale 0) fall into bin 0
       auto bin_of = [&](float x) { return (int)fminf(fmaxf((x - origin) * scale, 0.f), (float)(kBins - 1)); };
@@ -1563,7 +1573,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(D > 128 ? 2 :
         if (x * T < Pr) {
           bl[x] = bin_of(lf[x]);
           if constexpr (kRescore) bu[x] = bin_of(uf[x]);
-          if ((um >> x) & 1u) {
+          if (pending(x)) {
             atomicAdd(&hist[0][bl[x]], 1);
             if constexpr (kRescore) atomicAdd(&hist[1][bu[x]], 1);
           }
@@ -1582,17 +1592,19 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(D > 128 ? 2 :
       for (int x = 0; x < K; x++) {
         mu[x] = 0;
         if (x * T < Pr) {
-          const bool was = (um >> x) & 1u;
+          const bool was = pending(x);
           bool u = bl[x] >= t_lo;
           if constexpr (kRescore) u = bu[x] >= t_lo;
           const bool in = was && bl[x] > t_hi;
           u = u && was && !in;
-          um = u ? um : um & ~(1u << x);
+          if constexpr (kRescore) um = u ? um : um & ~(1u << x);
+          else um |= u ? 1u << x : 0u;
           mu[x] = __ballot(u);
           const uint64_t mi = __ballot(in);
           n_in += __popcll(mi);
           n_mine += __popcll(mu[x]);
-          sw.add(x, mi, ln);
+          if constexpr (kRescore) sw.add(x, mi, ln);
+          else sw.put(x, __ballot(in || (x * T + tid < P && !was)));   // forced pages are chosen
         }
       }
       sw.store(words, w, Pr);
@@ -1714,18 +1726,22 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(D > 128 ? 2 :
             }
           }
         };
-        Ids id;
-        Rows ra, rb;
         const int batches = (n_score + kAt * kRowsT - 1) / (kAt * kRowsT);   // uniform
         if (n_score <= 2 * kRowsT) {                               // uniform: all at once
           auto once = [&](auto n) {
-            load_ids(0, id, n);
-            load_rows(id, ra, n);
-            score(0, ra, n);
+            if (row16 < n_score) {                                 // waves without a page have no work
+              Ids id;
+              Rows ra;
+              load_ids(0, id, n);
+              load_rows(id, ra, n);
+              score(0, ra, n);
+            }
           };
           if (n_score <= kRowsT) once(std::integral_constant<int, 1>{});
           else once(std::integral_constant<int, 2>{});
         } else {
+          Ids id;
+          Rows ra, rb;
           using All = std::integral_constant<int, kAt>;
           load_ids(0, id, All{});
           load_rows(id, ra, All{});
